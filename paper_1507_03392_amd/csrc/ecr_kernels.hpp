@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 #include "ecr_device.hpp"
 #include "ecrpic.h"
 
@@ -15,6 +17,18 @@ namespace ecr {
 constexpr int kCoulCap = 256;
 constexpr int kCoulMaxE = 1024;
 static_assert(kBirthNone == ECR_BIRTH_NONE, "birth sentinel");
+
+// a launch whose error is its own (hipGetLastError could name an earlier
+// call's) and is left to no later call: what a read hands back rests on it
+template <typename... A, typename... B>
+hipError_t launch_checked(void (*kernel)(A...), dim3 grid, dim3 block, hipStream_t st, B &&...arg) {
+  return [&](A... a) {
+    void *p[] = {(void *)&a...};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, p, 0, st);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+  }(std::forward<B>(arg)...);
+}
 
 // Error bits raised by kernels (read back with the tallies).
 enum : uint32_t { ERR_COUL_OVERFLOW = 1, ERR_PARTNER_OVERFLOW = 2 };
@@ -89,7 +103,7 @@ void launch_coul_pairs(const KParams &P, const Tables *T, Soa<R> S, const uint32
                        const uint2 *counts, double *moments, StepArg step, hipStream_t st);
 int64_t coul_moment_slots(int64_t n);
 // (the tallies then to out as well, memory of the host, or null)
-void launch_sum_moments(const double *moments, int64_t nslots, DevAccum *acc, DevAccum *out, hipStream_t st);
+hipError_t launch_sum_moments(const double *moments, int64_t nslots, DevAccum *acc, DevAccum *out, hipStream_t st);
 
 // The fused step kernels (ecr_fused.hpp): the whole step in one kernel
 // (Coulomb pairing and collisions, push, wall/aperture loss, MCC, deposit),
@@ -195,8 +209,8 @@ void launch_sort(const KParams &P, Soa<R> A, Soa<R> B, const uint32_t *given, ui
 // the state by particle id into another set of arrays: q and species as bytes
 // of their own, cells from cellid.  bad: set when an id is out of range
 template <typename R>
-void launch_state_out(const Soa<R> &A, const uint32_t *cellid, int64_t n, const Soa<R> &out, uint8_t *species,
-                      uint32_t *cell, uint32_t *bad, hipStream_t st);
+hipError_t launch_state_out(const Soa<R> &A, const uint32_t *cellid, int64_t n, const Soa<R> &out, uint8_t *species,
+                            uint32_t *cell, uint32_t *bad, hipStream_t st);
 // a state given in order of id: charge states q (and birth, where there is a
 // step for an ion) to packed charges, ids and birth steps
 struct SpeciesEnds {

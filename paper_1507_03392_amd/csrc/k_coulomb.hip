@@ -516,8 +516,8 @@ __global__ void __launch_bounds__(kSumNT) k_sum_moments(const double *__restrict
 
 int64_t coul_moment_slots(int64_t n) { return ((n + kCoulCap - 1) / kCoulCap) * kMomentSlotsPerChunk; }
 
-void launch_sum_moments(const double *moments, int64_t nslots, DevAccum *acc, DevAccum *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_moments, dim3(1), dim3(kSumNT), 0, st, moments, nslots, acc, out);
+hipError_t launch_sum_moments(const double *moments, int64_t nslots, DevAccum *acc, DevAccum *out, hipStream_t st) {
+  return launch_checked(k_sum_moments, dim3(1), dim3(kSumNT), st, moments, nslots, acc, out);
 }
 
 int64_t coul_nchunks(int64_t n) { return (n + kCoulCap - 1) / kCoulCap; }

@@ -267,12 +267,12 @@ __global__ void __launch_bounds__(256) k_state_in(const uint8_t *__restrict__ q,
 }
 
 template <typename R>
-void launch_state_out(const Soa<R> &A, const uint32_t *cellid, int64_t n, const Soa<R> &out, uint8_t *species,
-                      uint32_t *cell, uint32_t *bad, hipStream_t st) {
-  launch_fill_u32(bad, 0u, 1, st);
-  if (n > 0)
-    hipLaunchKernelGGL(k_state_out<R>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, A, cellid, n, out, species,
-                       cell, bad);
+hipError_t launch_state_out(const Soa<R> &A, const uint32_t *cellid, int64_t n, const Soa<R> &out, uint8_t *species,
+                            uint32_t *cell, uint32_t *bad, hipStream_t st) {
+  const hipError_t e = launch_checked(k_fill_u32, dim3(1), dim3(64), st, bad, 0u, (int64_t)1);
+  if (e != hipSuccess || n <= 0) return e;
+  return launch_checked(k_state_out<R>, dim3((unsigned)((n + 255) / 256)), dim3(256), st, A, cellid, n, out, species,
+                        cell, bad);
 }
 void launch_state_in(const uint8_t *q, const uint32_t *birth, int64_t n, SpeciesEnds sp, uint8_t *qs, uint32_t *pid,
                      uint32_t *birth_out, hipStream_t st) {
@@ -280,10 +280,10 @@ void launch_state_in(const uint8_t *q, const uint32_t *birth, int64_t n, Species
     hipLaunchKernelGGL(k_state_in, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, q, birth, n, sp, qs, pid,
                        birth_out);
 }
-template void launch_state_out<double>(const Soa<double> &, const uint32_t *, int64_t, const Soa<double> &, uint8_t *,
-                                       uint32_t *, uint32_t *, hipStream_t);
-template void launch_state_out<float>(const Soa<float> &, const uint32_t *, int64_t, const Soa<float> &, uint8_t *,
-                                      uint32_t *, uint32_t *, hipStream_t);
+template hipError_t launch_state_out<double>(const Soa<double> &, const uint32_t *, int64_t, const Soa<double> &,
+                                             uint8_t *, uint32_t *, uint32_t *, hipStream_t);
+template hipError_t launch_state_out<float>(const Soa<float> &, const uint32_t *, int64_t, const Soa<float> &,
+                                            uint8_t *, uint32_t *, uint32_t *, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // self-test kernels

@@ -875,9 +875,10 @@ ecr_status get_state_t(ecr_run *r, ecr_state_view *v) {
   const Soa<R> B = soa<R>(r, 1 - r->cur);
   uint8_t *species = reinterpret_cast<uint8_t *>(B.pid);  // by now n bytes of 4 n
   uint32_t *cell = at<uint32_t>(r, r->L.key), *bad = at<uint32_t>(r, r->L.bsum);
-  launch_state_out<R>(soa<R>(r, r->cur), at<uint32_t>(r, r->L.cellid), n, B, species, cell, bad, r->stream);
   uint32_t hbad = 0;
-  hipError_t e = hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, r->stream);
+  hipError_t e =
+      launch_state_out<R>(soa<R>(r, r->cur), at<uint32_t>(r, r->L.cellid), n, B, species, cell, bad, r->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, r->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(r->stream);
   if (e != hipSuccess) return check_hip(r, e, "get_state");
   if (hbad) return fail(r, ECR_ESTATE, "corrupt particle ids");
@@ -1368,13 +1369,14 @@ ecr_status ecr_read_tallies(ecr_run *r, ecr_tallies *out) {
         hipSuccess) {
       (void)hipGetLastError();
       r->host_acc = nullptr;
+    } else {
+      memset(r->host_acc, 0, sizeof(DevAccum));
     }
     if (ex) (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
-  launch_sum_moments(at<double>(r, r->L.moments), moment_slots(&r->p), at<DevAccum>(r, r->L.acc), r->host_acc,
-                     r->stream);
-  hipError_t e = hipSuccess;
-  if (!r->host_acc)
+  hipError_t e = launch_sum_moments(at<double>(r, r->L.moments), moment_slots(&r->p), at<DevAccum>(r, r->L.acc),
+                                    r->host_acc, r->stream);
+  if (e == hipSuccess && !r->host_acc)
     e = hipMemcpyAsync(&h, at<DevAccum>(r, r->L.acc), sizeof(DevAccum), hipMemcpyDeviceToHost, r->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(r->stream);
   if (e != hipSuccess) return check_hip(r, e, "read_tallies");
