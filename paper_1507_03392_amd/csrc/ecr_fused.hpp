@@ -219,12 +219,12 @@ __device__ __forceinline__ Box make_box(const KParams &P, const int bb[6], int c
   return b;
 }
 __device__ __forceinline__ void cell_box(const ChunkEntry &E, int bb[6]) {
-  bb[0] = (int)(E.x & 0xffffu);
-  bb[1] = (int)(E.y & 0xffffu);
-  bb[2] = (int)(E.z & 0xffffu);
-  bb[3] = (int)(E.x >> 16);
-  bb[4] = (int)(E.y >> 16);
-  bb[5] = (int)(E.z >> 16);
+  bb[0] = (int)E.x;
+  bb[1] = (int)E.y;
+  bb[2] = (int)E.z;
+  bb[3] = (int)(E.x + (E.wxy & 0xffffu));
+  bb[4] = (int)(E.y + (E.wxy >> 16));
+  bb[5] = (int)(E.z + E.wz);
 }
 
 // a brick's nf fields to HBM (field f of it to field f of the densities, the
@@ -288,8 +288,8 @@ __device__ __forceinline__ void fused_wg(const StepBatch<R> &B, const uint32_t n
       const KParams &P = fresh<R>(job).P;
       const uint32_t c = P.cellid[lo], r = c / (uint32_t)P.nx, lg = 31u - (uint32_t)__clz((int)(end - lo));
       const uint32_t x = c - r * (uint32_t)P.nx, y = r % (uint32_t)P.ny, z = r / (uint32_t)P.ny;
-      const ChunkEntry M[2] = {{lo, lo + kPSlots, x | (x << 16), y | (y << 16), z | (z << 16), 0u, 0u, 0u},
-                               {lo + kPSlots, end, x | (x << 16), y | (y << 16), z | (z << 16), 1u << lg, 1u, 0u}};
+      const ChunkEntry M[2] = {{lo, lo + kPSlots, x, y, z, 0u, 0u, 0u},
+                               {lo + kPSlots, end, x, y, z, 0u, 0u, (1u << lg) | (1u << 16)}};
       for (uint32_t it = 0; it < nsteps; ++it) {
         medium(job, M, mslot, step0 + it);
         __syncthreads();

@@ -118,10 +118,12 @@ hipError_t launch_sum_moments(const double *moments, int64_t nslots, DevAccum *a
 // cell of m slots, numbered from the chunk's first), its cell's number in the
 // chunk and whether it is the cell's first slot
 struct ChunkEntry {
-  uint32_t lo, end;           // slots [lo, end)
-  uint32_t x, y, z;           // the box of its cells: lowest | highest << 16 of each index
-  uint32_t nbuckets, ncells;
-  uint32_t pad;
+  uint32_t lo, end;  // slots [lo, end)
+  uint32_t x, y, z;  // the box of its cells: the lowest index along each axis,
+  uint32_t wxy, wz;  // and highest - lowest, x | y << 16 and z (at most 65535: no wider box has a brick)
+  uint32_t nn;       // buckets | cells << 16
+  __host__ __device__ uint32_t buckets() const { return nn & 0xffffu; }
+  __host__ __device__ uint32_t cells() const { return nn >> 16; }
 };
 struct ChunkTable {
   uint32_t *cnt;

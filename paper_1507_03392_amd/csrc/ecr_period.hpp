@@ -69,7 +69,7 @@ __device__ __forceinline__ void order_wave(const JobPtr<R> job, const ChunkEntry
   constexpr int kG = 4;  // draws interleaved
   constexpr int kN = kPSlots / 64;
   const int lane = threadIdx.x & 63;
-  const int nsl = (int)(E.end - E.lo), nb = (int)E.nbuckets;
+  const int nsl = (int)(E.end - E.lo), nb = (int)E.buckets();
   const StepJob<R> &J = fresh<R>(job);
   const KParams &P = J.P;
   Ordering<kPSlots> &o = sh.o;
@@ -124,7 +124,7 @@ __device__ __forceinline__ void order_wave(const JobPtr<R> job, const ChunkEntry
       o.bkey[o.hist[at[r] & 0x3ffu] + ((at[r] >> 10) & 0x3ffu)] =
           ((uint64_t)key[r] << 32) | sh.sid[lane + 64 * r];
   });
-  number_items(o, (int)E.ncells, nb, tot + 2 * buf);
+  number_items(o, (int)E.cells(), nb, tot + 2 * buf);
   fence();
   rounds<kN>([&](auto rc) __attribute__((always_inline)) {
     constexpr int r = decltype(rc)::value;
@@ -178,7 +178,7 @@ __device__ __forceinline__ void chunk_steps(const JobPtr<R> job, const ChunkEntr
       y[k] = S.y[j[k]];
       z[k] = S.z[j[k]];
     }
-    if (tid == 0) sh.o.cellb[E.ncells] = (uint16_t)E.nbuckets;
+    if (tid == 0) sh.o.cellb[E.cells()] = (uint16_t)E.buckets();
 #pragma unroll
     for (int k = 0; k < kRounds; ++k) {
       if (tid + k * kNT < nsl) {

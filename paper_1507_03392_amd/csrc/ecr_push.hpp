@@ -301,14 +301,14 @@ constexpr int kStage = kPad(kTile);
 template <typename R, int TILE = kTile>
 struct alignas(16) DepStage {
   R t[3][TILE];
-  uint16_t c[3][TILE];
+  uint32_t c[TILE];  // pack_cell
   uint8_t q[TILE];  // charge, or 0xFF: nothing to deposit
 };
 
-// the brick reuses the staging memory: as many doubles as binary64 staging holds
+// the brick reuses the staging memory: 31 bytes a slot
 template <int TILE>
 constexpr int dep_brick() {
-  return (int)(sizeof(DepStage<double, TILE>) / sizeof(double));
+  return 31 * TILE / (int)sizeof(double);
 }
 constexpr int kDepBrick = dep_brick<kTile>();
 
@@ -422,9 +422,7 @@ __device__ __forceinline__ void stage_cic(const KParams &P, DepStage<R, TILE> &s
   st.t[0][k] = tx;
   st.t[1][k] = ty;
   st.t[2][k] = tz;
-  st.c[0][k] = (uint16_t)ix;
-  st.c[1][k] = (uint16_t)iy;
-  st.c[2][k] = (uint16_t)iz;
+  st.c[k] = pack_cell(P, ix, iy, iz);
   st.q[k] = on ? (uint8_t)q : (uint8_t)0xFF;
   if (on) {
     mn[0] = min(mn[0], ix);
@@ -491,17 +489,14 @@ __device__ __forceinline__ void deposit_staged(const KParams &P, double *__restr
     lds_load4(&sh.st.t[1][k0], D.ty);
     lds_load4(&sh.st.t[2][k0], D.tz);
     const uint32_t q4 = *reinterpret_cast<const uint32_t *>(&sh.st.q[k0]);
-    uint2 c4[3];
-    for (int a = 0; a < 3; ++a) c4[a] = *reinterpret_cast<const uint2 *>(&sh.st.c[a][k0]);
+    const uint4 c4 = *reinterpret_cast<const uint4 *>(&sh.st.c[k0]);
+    const uint32_t c[kP] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
     for (int p = 0; p < kP; ++p) {
       const uint8_t q = (uint8_t)(q4 >> (8 * p));
       D.on[p] = q != 0xFF;
       D.q[p] = q;
-      const int sh16 = 16 * (p & 1);
-      D.ix[p] = (int)(((p < 2 ? c4[0].x : c4[0].y) >> sh16) & 0xffffu);
-      D.iy[p] = (int)(((p < 2 ? c4[1].x : c4[1].y) >> sh16) & 0xffffu);
-      D.iz[p] = (int)(((p < 2 ? c4[2].x : c4[2].y) >> sh16) & 0xffffu);
+      unpack_cell(P, c[p], D.ix[p], D.iy[p], D.iz[p]);
     }
   }
   // the box is the same for every lane: keep it in scalar registers

@@ -28,7 +28,7 @@ struct OneShared {
   uint32_t sid[kOSlots];
   union {
     WorkList<kOSlots> item;
-    uint64_t base[kOSlots];  // after the push: base cell | charge << 48, 255 for none
+    uint64_t base[kOSlots];  // after the push: base cell (pack_cell) | charge << 32, 255 for none
   };
   uint8_t sqs[kOSlots];
   double cacc[5 * 64];  // the collisions' momentum and energy sums, an entry per lane number
@@ -54,8 +54,8 @@ __device__ __forceinline__ void chunk_step(const JobPtr<R> job, const ChunkEntry
   const int tid = threadIdx.x;
   const int64_t lo[2] = {E[0].lo, two ? E[1].lo : 0u};
   const int n[2] = {(int)(E[0].end - E[0].lo), two ? (int)(E[1].end - E[1].lo) : 0};
-  const int nb0 = (int)E[0].nbuckets, nh0 = (int)E[0].ncells;
-  const int nb = nb0 + (two ? (int)E[1].nbuckets : 0), nh = nh0 + (two ? (int)E[1].ncells : 0);
+  const int nb0 = (int)E[0].buckets(), nh0 = (int)E[0].cells();
+  const int nb = nb0 + (two ? (int)E[1].buckets() : 0), nh = nh0 + (two ? (int)E[1].cells() : 0);
   const bool coul = (job->P.pmask & P_COULOMB) != 0 && n[0] + n[1] >= 2;
   const bool mcc = needs_mcc_uniform(fresh<R>(job).P);
   const uint32_t dm = job->dens ? (NQ ? 3u : job->P.dmask & 7u) : 0u;
@@ -231,7 +231,7 @@ __device__ __forceinline__ void chunk_step(const JobPtr<R> job, const ChunkEntry
         sh.v[q] = tx;
         sh.v[kOSlots + q] = ty;
         sh.v[2 * kOSlots + q] = tz;
-        sh.base[q] = (uint64_t)(uint32_t)(ix | (iy << 16)) | ((uint64_t)(uint32_t)(iz | ((on ? Q : 255) << 16)) << 32);
+        sh.base[q] = pack_cell(P, ix, iy, iz) | ((uint64_t)(uint32_t)(on ? Q : 255) << 32);
       }
     }
     if (EXT && chg_next) add_charge(chg_next, ccell, cq);  // all lanes: the run sums use lane moves
@@ -306,10 +306,8 @@ __device__ __forceinline__ void chunk_step(const JobPtr<R> job, const ChunkEntry
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const uint64_t b = sh.base[q0 + p];
-      D.ix[p] = (int)((uint32_t)b & 0xffffu);
-      D.iy[p] = (int)((uint32_t)b >> 16);
-      D.iz[p] = (int)((uint32_t)(b >> 32) & 0xffffu);
-      D.q[p] = (int)(b >> 48);
+      unpack_cell(J.P, (uint32_t)b, D.ix[p], D.iy[p], D.iz[p]);
+      D.q[p] = (int)(b >> 32);
       D.on[p] = j0 + p < (c ? n[1] : n[0]) && D.q[p] != 255;
     }
   }

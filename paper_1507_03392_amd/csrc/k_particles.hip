@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(kBlock) k_deposit(KParams P, Soa<R> S, double 
 template <typename R>
 struct PStage {
   R t[3][kStage];
-  uint16_t c[3][kStage];
+  uint32_t c[kStage];  // pack_cell
   double e[kStage];  // M |v|^2 / 3, or < 0: nothing to deposit
 };
 
@@ -196,9 +196,7 @@ __global__ void __launch_bounds__(kBlock) k_deposit_pressure(KParams P, Soa<R> S
         sh.st.t[0][k] = tx;
         sh.st.t[1][k] = ty;
         sh.st.t[2][k] = tz;
-        sh.st.c[0][k] = (uint16_t)ix;
-        sh.st.c[1][k] = (uint16_t)iy;
-        sh.st.c[2][k] = (uint16_t)iz;
+        sh.st.c[k] = pack_cell(P, ix, iy, iz);
         sh.st.e[k] = (P.mass[sp_of(qs)] * (double)((vx * vx + vy * vy) + vz * vz)) / 3.0;
         mn[0] = min(mn[0], ix);
         mn[1] = min(mn[1], iy);
@@ -221,9 +219,7 @@ __global__ void __launch_bounds__(kBlock) k_deposit_pressure(KParams P, Soa<R> S
     tx[p] = sh.st.t[0][k];
     ty[p] = sh.st.t[1][k];
     tz[p] = sh.st.t[2][k];
-    ix[p] = sh.st.c[0][k];
-    iy[p] = sh.st.c[1][k];
-    iz[p] = sh.st.c[2][k];
+    unpack_cell(P, sh.st.c[k], ix[p], iy[p], iz[p]);
   }
   int bb[6];
   box_reduce<kBlock>(box, bb);

@@ -188,12 +188,12 @@ __global__ void __launch_bounds__(kPrepNT) k_step_prep(KParams P, int fill, Chun
     const int *b = box[tid];
     C.chunk[cbase + tid] = {(uint32_t)(lo + cs[cb[tid]]),
                             (uint32_t)(lo + cell_end(ce[tid] - 1)),
-                            (uint32_t)(b[0] | (b[3] << 16)),
-                            (uint32_t)(b[1] | (b[4] << 16)),
-                            (uint32_t)(b[2] | (b[5] << 16)),
-                            nbs[ce[tid]] - nbs[cb[tid]],
-                            (uint32_t)(ce[tid] - cb[tid]),
-                            0u};
+                            (uint32_t)b[0],
+                            (uint32_t)b[1],
+                            (uint32_t)b[2],
+                            (uint32_t)(min(b[3] - b[0], 0xffff) | (min(b[4] - b[1], 0xffff) << 16)),
+                            (uint32_t)min(b[5] - b[2], 0xffff),
+                            (nbs[ce[tid]] - nbs[cb[tid]]) | ((uint32_t)(ce[tid] - cb[tid]) << 16)};
   }
   for (int i = tid; i < total; i += kPrepNT) {
     // the slot's cell: the last head at or before it

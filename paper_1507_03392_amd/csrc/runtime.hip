@@ -372,6 +372,9 @@ void derive(const ecr_params *p, KParams &K, Tables &T, double &weight) {
   K.c3 = p->BH_T / R02;
   K.c4 = ((2.0 * p->mirror_k) * p->B0_T) / L2;
   K.dt = dt;
+  const auto bits = [](int32_t n) -> uint32_t { return n > 1 ? 32u - (uint32_t)__builtin_clz((unsigned)n - 1u) : 0u; };
+  K.ybits = bits(p->nx);
+  K.zbits = K.ybits + bits(p->ny);
   const double vzone = (4.0 / 3.0) * kPi * (p->zone_a_m * p->zone_a_m) * p->zone_c_m;
   weight = p->weight > 0.0 ? p->weight
                            : (p->n_particles > 0 ? p->ne_in_m3 * vzone / (double)p->n_particles : 0.0);
