@@ -96,10 +96,11 @@ __device__ __forceinline__ bool needs_mcc_uniform(const KParams &P) {
   return (P.pmask & (P_IONIZE | P_CX | P_ELASTIC)) != 0;
 }
 
-// the Monte-Carlo uniform if it can lie below p, else its lower bound
+// the Monte-Carlo uniform if it can lie below p (or p is not a number, and
+// the channels before it count), else its lower bound
 __device__ __forceinline__ double mcc_uniform(const KParams &P, uint32_t id, uint32_t step, uint32_t w0, double p) {
   double u = (double)(w0 >> 5) * 0x1p-27;
-  if (u < p) [[unlikely]] {
+  if (!(u >= p)) [[unlikely]] {
     const uint4 W = draw(P, id, step, S_STEP, 0);
     u = u53(W.x, W.y);
   }
