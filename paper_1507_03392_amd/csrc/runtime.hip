@@ -1003,13 +1003,62 @@ ecr_status ecr_footprint(const ecr_params *params, size_t *device_bytes) {
 
 namespace {
 
-// release what a run holds besides its arena: events and captured graphs
-void release_run(ecr_run *r) {
-  if (r->host_acc) {
-    (void)hipStreamSynchronize(r->stream);
-    (void)hipHostFree(r->host_acc);
-    r->host_acc = nullptr;
+// Pinned memory for the tallies' way to the host: a block per run from its
+// first read on.  A run's end leaves its block to the runs to come, up to
+// kMaxPinned of them: to free pinned memory waits for everything that the
+// device does, and a run's end is to wait for nothing.  A block is idle
+// between two reads (each waits for the kernel that fills it).
+std::mutex g_pinned_mu;
+constexpr int kMaxPinned = 64;
+DevAccum *g_pinned[kMaxPinned];
+int g_npinned = 0;
+
+// neither refused for, nor a hindrance to, a capture of some other stream
+struct BesideCaptures {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  ~BesideCaptures() {
+    if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
+};
+
+// null where there is none to be had
+DevAccum *take_pinned() {
+  DevAccum *p = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    if (g_npinned > 0) p = g_pinned[--g_npinned];
+  }
+  if (!p) {
+    const BesideCaptures relaxed;
+    if (hipHostMalloc((void **)&p, sizeof(DevAccum), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+  }
+  memset(p, 0, sizeof(DevAccum));
+  return p;
+}
+
+// idle: no kernel may still write it
+void give_pinned(DevAccum *p, bool idle) {
+  if (!p) return;
+  if (idle) {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    if (g_npinned < kMaxPinned) {
+      g_pinned[g_npinned++] = p;
+      return;
+    }
+  }
+  const BesideCaptures relaxed;
+  (void)hipHostFree(p);
+}
+
+// release what a run holds besides its arena: the tallies' block, events and
+// captured graphs
+void release_run(ecr_run *r) {
+  give_pinned(r->host_acc, !r->failed);
+  r->host_acc = nullptr;
   forget_batch_graphs(r);
   harvest(r);
   for (auto e : r->free_events) (void)hipEventDestroy(e);
@@ -1364,19 +1413,7 @@ ecr_status ecr_step_batch(ecr_run *const *runs, int32_t n_runs, int64_t n_steps,
 ecr_status ecr_read_tallies(ecr_run *r, ecr_tallies *out) {
   if (!r || !out) return fail(r, ECR_EINVAL, "NULL argument");
   DevAccum h;
-  if (!r->host_acc && !r->is_static) {
-    // (not refused for, nor a hindrance to, a capture of some other stream)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const bool ex = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    if (hipHostMalloc((void **)&r->host_acc, sizeof(DevAccum), hipHostMallocPortable | hipHostMallocMapped) !=
-        hipSuccess) {
-      (void)hipGetLastError();
-      r->host_acc = nullptr;
-    } else {
-      memset(r->host_acc, 0, sizeof(DevAccum));
-    }
-    if (ex) (void)hipThreadExchangeStreamCaptureMode(&mode);
-  }
+  if (!r->host_acc && !r->is_static) r->host_acc = take_pinned();
   hipError_t e = launch_sum_moments(at<double>(r, r->L.moments), moment_slots(&r->p), at<DevAccum>(r, r->L.acc),
                                     r->host_acc, r->stream);
   if (e == hipSuccess && !r->host_acc)

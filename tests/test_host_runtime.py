@@ -1,5 +1,6 @@
 """The library's host code over a stub of the HIP runtime (no device): what
-the calls that hand results back do when their launch is refused."""
+the calls that hand results back do when their launch is refused, and what a
+run's end waits for."""
 import os
 import shutil
 import subprocess
@@ -82,4 +83,33 @@ for at in range(3):
     stub.stub_refuse(at)
     assert L.ecr_set_state(run, C.byref(v)) == -3
     run, keep = create(300, precision={precision})
+""")
+
+
+def test_a_runs_end_waits_for_nothing(stub):
+    # the tallies' pinned memory goes to the runs to come, a bounded part of
+    # it; to free pinned memory waits for the whole device
+    host(stub, """
+t = ecr.Tallies()
+for _ in range(100):  # one after another
+    run, keep = create(40)
+    assert L.ecr_read_tallies(run, C.byref(t)) == 0
+    before = stub.stub_syncs(), stub.stub_host_frees()
+    assert L.ecr_destroy(run) == 0
+    assert (stub.stub_syncs(), stub.stub_host_frees()) == before
+assert stub.stub_host_allocs() == 1
+runs = [create(40) for _ in range(90)]  # at once
+for r, _ in runs:
+    assert L.ecr_read_tallies(r, C.byref(t)) == 0
+assert stub.stub_host_allocs() == 90
+for r, _ in runs:
+    assert L.ecr_destroy(r) == 0
+assert stub.stub_host_frees() == 90 - 64
+# a run that failed may have a kernel about: its block is freed
+run, keep = create(40)
+assert L.ecr_read_tallies(run, C.byref(t)) == 0
+stub.stub_refuse(0)
+assert L.ecr_read_tallies(run, C.byref(t)) == -3
+assert L.ecr_destroy(run) == 0
+assert stub.stub_host_frees() == 90 - 64 + 1 and stub.stub_host_allocs() == 90
 """)
