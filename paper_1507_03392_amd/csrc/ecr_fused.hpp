@@ -266,9 +266,10 @@ __device__ __forceinline__ void add_moments(const double *cacc, double *__restri
 // table, their number, moment slot): workgroup wg's chunks.  medium(job,
 // entries, moment slot, step): one step of a cell of up to 2 kPSlots slots.
 template <typename R, int FLD, bool EXT, bool PR, int LDSB, typename F, typename G>
-__device__ __forceinline__ void fused_wg(const StepBatch<R> &B, const uint32_t nsteps,
-                                         const uint32_t *__restrict__ chg_cur, uint32_t *__restrict__ chg_next,
+__device__ __forceinline__ void fused_wg(const StepBatch<R> &B, const uint32_t nsteps, const CellGrids &grids,
                                          void *lds, F &&chunks, G &&medium) {
+  const uint32_t *__restrict__ chg_cur = grids.cur;
+  uint32_t *__restrict__ chg_next = grids.next;
   __shared__ uint32_t red[kNW], gcount;
   int run = 0;
   for (int t = 1; t < B.n; ++t) run = blockIdx.x >= B.wg0[t] ? t : run;
@@ -302,6 +303,15 @@ __device__ __forceinline__ void fused_wg(const StepBatch<R> &B, const uint32_t n
                                            J.dens, mslot, J.scratch64, step0 + it, chg_cur, chg_next,
                                            (unsigned char *)lds, red, &gcount);
     }
+  }
+  // the grid that the step before read, for the step to come to add to: a
+  // fill of its own between two steps took 4-5 us of 61 at 600k ions, and
+  // these stores, after everything that waits for a load, cost next to none
+  if (EXT && grids.clear) {
+    uint4 *c = reinterpret_cast<uint4 *>(grids.clear);
+    const int64_t n4 = grids.n / 4, i0 = (int64_t)blockIdx.x * kNT + threadIdx.x;
+    for (int64_t i = i0; i < n4; i += (int64_t)gridDim.x * kNT) c[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 < grids.n - 4 * n4) grids.clear[4 * n4 + i0] = 0u;
   }
 }
 

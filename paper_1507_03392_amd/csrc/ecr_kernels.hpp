@@ -183,14 +183,22 @@ struct SetWords {
   uint32_t val[kMaxBatch];
   int n;
 };
+// the cell grids of a run that has them (the only one of its launch): the
+// step reads cur and adds to next, zeroed before, and sets n words at clear
+// (or none) to zero
+struct CellGrids {
+  const uint32_t *cur;
+  uint32_t *next, *clear;
+  int64_t n;
+};
+// cur's n words to home, then zero to clear (which may be cur)
+void launch_grids_home(const uint32_t *cur, uint32_t *home, uint32_t *clear, int64_t n, hipStream_t st);
+
 // ext: optional physics (step_ext); fields: node grids of E or B.
-// One step; nq: exactly the ion number and charge are deposited; chg_cur,
-// chg_next: the cell grids of a run that has them (the only one of its
-// launch), chg_next zeroed before
+// One step; nq: exactly the ion number and charge are deposited
 bool step_ext(const KParams &P);
 template <typename R>
-void launch_step(const StepBatch<R> &B, bool nq, bool ext, bool fields, const uint32_t *chg_cur, uint32_t *chg_next,
-                 hipStream_t st);
+void launch_step(const StepBatch<R> &B, bool nq, bool ext, bool fields, const CellGrids &grids, hipStream_t st);
 // nsteps steps in one launch, the state on chip from the first to the last;
 // for runs without cell grids (nothing then couples two chunks between
 // sorts).  pressure: with the ion pressure field

@@ -384,7 +384,7 @@ k_period(StepBatch<R> B, uint32_t nsteps) {
   __shared__ uint32_t tot[5 + kNW];
   static_assert(sizeof(OneShared<R>) <= sizeof(lds), "a medium cell's step fits");
   fused_wg<R, FLD, EXT, PR, (int)sizeof(lds)>(
-      B, nsteps, nullptr, nullptr, &lds,
+      B, nsteps, CellGrids{}, &lds,
       [&](const JobPtr<R> job, uint32_t step0, uint32_t e, uint32_t stride, const ChunkEntry *chunk, uint32_t nchunk,
           double *mslot) __attribute__((always_inline)) {
         const int turn = 64 * (int)(e % kNW);

@@ -348,12 +348,12 @@ __device__ __forceinline__ void chunk_step(const JobPtr<R> job, const ChunkEntry
 // one step (four workgroups per CU, by the LDS and by the registers)
 template <typename R, int FLD, bool EXT, bool NQ>
 __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_step(StepBatch<R> B, const uint32_t *__restrict__ chg_cur, uint32_t *__restrict__ chg_next) {
+k_step(StepBatch<R> B, CellGrids grids) {
   __shared__ __align__(16) OneShared<R> sh;
   __shared__ uint32_t wsum[kNW], tot[2];
   static_assert(sizeof(sh) + 64 <= 40 * 1024, "four workgroups share a CU's 160 KB");
   fused_wg<R, FLD, EXT, false, (int)sizeof(sh)>(
-      B, 1u, chg_cur, chg_next, &sh,
+      B, 1u, grids, &sh,
       [&](const JobPtr<R> job, uint32_t step, uint32_t e, uint32_t stride, const ChunkEntry *table, uint32_t nchunk,
           double *mslot) __attribute__((always_inline)) {
         const int turn = 64 * (int)(e % kNW);
@@ -364,8 +364,8 @@ k_step(StepBatch<R> B, const uint32_t *__restrict__ chg_cur, uint32_t *__restric
         // not wait for the number of chunks
         ChunkEntry E[2] = {entry(chunk, e), entry(chunk, e + 1)};
         while (e < nchunk) {
-          chunk_step<R, FLD, EXT, NQ>(job, E, per == 2u && e + 1 < nchunk, mslot, step, sh, wsum, tot, turn, chg_cur,
-                                      chg_next);
+          chunk_step<R, FLD, EXT, NQ>(job, E, per == 2u && e + 1 < nchunk, mslot, step, sh, wsum, tot, turn, grids.cur,
+                                      grids.next);
           __syncthreads();  // the next ones reuse the LDS
           e += per * stride;
           if (e < nchunk) {
@@ -375,27 +375,25 @@ k_step(StepBatch<R> B, const uint32_t *__restrict__ chg_cur, uint32_t *__restric
         }
       },
       [&](const JobPtr<R> job, const ChunkEntry(&M)[2], double *mslot, uint32_t step) __attribute__((always_inline)) {
-        chunk_step<R, FLD, EXT, NQ>(job, M, true, mslot, step, sh, wsum, tot, 0, chg_cur, chg_next);
+        chunk_step<R, FLD, EXT, NQ>(job, M, true, mslot, step, sh, wsum, tot, 0, grids.cur, grids.next);
       });
 }
 
 }  // namespace
 
 template <typename R, int FLD, bool EXT>
-static void launch_step_e(const StepBatch<R> &B, bool nq, const uint32_t *chg_cur, uint32_t *chg_next,
-                          hipStream_t st) {
+static void launch_step_e(const StepBatch<R> &B, bool nq, const CellGrids &grids, hipStream_t st) {
   const dim3 g(B.wg0[B.n]), b(kNT);
-  if (nq) hipLaunchKernelGGL((k_step<R, FLD, EXT, true>), g, b, 0, st, B, chg_cur, chg_next);
-  else hipLaunchKernelGGL((k_step<R, FLD, EXT, false>), g, b, 0, st, B, chg_cur, chg_next);
+  if (nq) hipLaunchKernelGGL((k_step<R, FLD, EXT, true>), g, b, 0, st, B, grids);
+  else hipLaunchKernelGGL((k_step<R, FLD, EXT, false>), g, b, 0, st, B, grids);
 }
 
 template <typename R>
-void launch_step(const StepBatch<R> &B, bool nq, bool ext, bool fields, const uint32_t *chg_cur, uint32_t *chg_next,
-                 hipStream_t st) {
+void launch_step(const StepBatch<R> &B, bool nq, bool ext, bool fields, const CellGrids &grids, hipStream_t st) {
   if (B.n <= 0 || B.wg0[B.n] == 0) return;
-  if (fields) launch_step_e<R, 7, true>(B, nq, chg_cur, chg_next, st);
-  else if (ext || chg_cur) launch_step_e<R, 0, true>(B, nq, chg_cur, chg_next, st);
-  else launch_step_e<R, 0, false>(B, nq, nullptr, nullptr, st);
+  if (fields) launch_step_e<R, 7, true>(B, nq, grids, st);
+  else if (ext || grids.cur) launch_step_e<R, 0, true>(B, nq, grids, st);
+  else launch_step_e<R, 0, false>(B, nq, CellGrids{}, st);
 }
 
 }  // namespace ecr

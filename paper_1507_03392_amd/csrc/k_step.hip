@@ -259,6 +259,19 @@ void launch_set_job(const StepJob<R> &J, StepJob<R> *dst, hipStream_t st) {
   hipLaunchKernelGGL((k_set_job<R>), dim3(1), dim3(64), 0, st, J, dst);
 }
 
+__global__ void __launch_bounds__(256) k_grids_home(const uint32_t *cur, uint32_t *home, uint32_t *clear, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    home[i] = cur[i];
+    clear[i] = 0u;
+  }
+}
+
+void launch_grids_home(const uint32_t *cur, uint32_t *home, uint32_t *clear, int64_t n, hipStream_t st) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL(k_grids_home, dim3((unsigned)(n < 1048576 ? (n + 255) / 256 : 4096)), dim3(256), 0, st, cur, home,
+                     clear, n);
+}
+
 void launch_set_words(const SetWords &w, hipStream_t st) {
   if (w.n > 0) hipLaunchKernelGGL(k_set_words, dim3(1), dim3(64), 0, st, w);
 }
@@ -266,7 +279,6 @@ void launch_set_words(const SetWords &w, hipStream_t st) {
 template void launch_set_job<double>(const StepJob<double> &, StepJob<double> *, hipStream_t);
 template void launch_set_job<float>(const StepJob<float> &, StepJob<float> *, hipStream_t);
 template void launch_period<double>(const StepBatch<double> &, uint32_t, bool, bool, bool, hipStream_t);
-template void launch_step<double>(const StepBatch<double> &, bool, bool, bool, const uint32_t *, uint32_t *,
-                                  hipStream_t);
+template void launch_step<double>(const StepBatch<double> &, bool, bool, bool, const CellGrids &, hipStream_t);
 
 }  // namespace ecr

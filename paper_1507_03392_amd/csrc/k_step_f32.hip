@@ -5,7 +5,6 @@
 namespace ecr {
 
 template void launch_period<float>(const StepBatch<float> &, uint32_t, bool, bool, bool, hipStream_t);
-template void launch_step<float>(const StepBatch<float> &, bool, bool, bool, const uint32_t *, uint32_t *,
-                                 hipStream_t);
+template void launch_step<float>(const StepBatch<float> &, bool, bool, bool, const CellGrids &, hipStream_t);
 
 }  // namespace ecr

@@ -39,7 +39,8 @@ struct Layout {
       bfield, evlog;
   size_t pcnt, pchunk, pbig;  // the fused step's chunk table (its per-slot buckets reuse the sort's rank array)
   size_t scratch64;  // sort space of the pools that exceed the LDS (fused kernel)
-  size_t chg[2];  // ion charge per cell, double-buffered (ECR_FLAG_SELF_NE)
+  size_t chg[3];  // ion charge per cell, of the steps in turn (ECR_FLAG_SELF_NE)
+  int ngrids;     // two or three of them
   size_t cxreq;   // exchanges per species and collision cell (ECR_FLAG_CX_PARTNER)
   size_t cxchunk; // per Coulomb chunk: any of them in its cells
   size_t bden;    // |B| hx per cell (heating kick with self-consistent electrons)
@@ -90,7 +91,13 @@ Layout make_layout(const ecr_params *p) {
   L.pchunk = align_up(L.pcnt + 8);
   L.pbig = align_up(L.pchunk + sizeof(ChunkEntry) * (size_t)step_max_chunks((int64_t)N));
   const size_t table_end = align_up(L.pbig + 8 * (size_t)step_max_big((int64_t)N));
+  const size_t grid = 4 * (size_t)ncells(p) * (size_t)(1 + p->n_species);
   o = align_up(o + sizeof(CoulItem) * kCoulItems * (size_t)coul_nchunks((int64_t)N));
+  // the fused step's third cell grid where it fits that space (24 bytes a
+  // particle): runs of fewer particles than a fifth of the grid's words, whose
+  // steps are short of work rather than of launches, have two
+  L.chg[2] = table_end;
+  L.ngrids = !(p->flags & ECR_FLAG_SPLIT) && table_end + grid <= o ? 3 : 2;
   o = o > table_end ? o : table_end;
   L.tris = o;  // per-chunk (pairs, triplets) counts
   o = align_up(o + 8 * (size_t)coul_nchunks((int64_t)N));
@@ -120,8 +127,7 @@ Layout make_layout(const ecr_params *p) {
   if (p->flags & ECR_FLAG_EVENTS) o = align_up(o + N);
   for (int b = 0; b < 2; ++b) {
     L.chg[b] = o;
-    if (p->flags & (ECR_FLAG_SELF_NE | ECR_FLAG_SELF_N0))
-      o = align_up(o + 4 * (size_t)ncells(p) * (size_t)(1 + p->n_species));
+    if (p->flags & (ECR_FLAG_SELF_NE | ECR_FLAG_SELF_N0)) o = align_up(o + grid);
   }
   L.cxreq = o;
   if (p->flags & ECR_FLAG_CX_PARTNER) o = align_up(o + 4 * (size_t)ncells(p) * (size_t)p->n_species);
@@ -253,8 +259,8 @@ struct ecr_run {
   std::vector<Pending> pending;
   // one sort period (sort_every steps, starting with its sort) captured as a
   // HIP graph, one per SoA buffer the period starts from
-  hipGraphExec_t gexec[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // [SoA buffer][charge grid]
-  int chg_par = 0;  // charge grid of the current step (ECR_FLAG_SELF_NE)
+  hipGraphExec_t gexec[2] = {nullptr, nullptr};
+  int chg_par = 0;  // cell grid of the current step, of L.ngrids; 0 at the start of a captured period
   // where the device puts the tallies for ecr_read_tallies, from its first
   // call on (pinned; null: they are copied)
   DevAccum *host_acc = nullptr;
@@ -538,9 +544,25 @@ bool field_grids(const ecr_run *r) { return r->p.efield_nodes || r->kp.bmap; }
 // the whole step in one kernel; ECR_FLAG_SPLIT (per-kernel timing) runs it
 // as separate kernels
 bool fused(const ecr_run *r) { return !(r->p.flags & ECR_FLAG_SPLIT); }
-// the partners' kernel, the last of such a run's steps, clears the grids that
-// the step has read: those of the step to come are zero between steps
-bool grids_clear(const ecr_run *r) { return fused(r) && cell_grids(r) && r->kp.cxreq && r->kp.n > 0; }
+// With three cell grids a step clears the one that the step before read; with
+// two, the partners' kernel, the last of such a run's steps, clears the one
+// that the step has read.  Either way the grid of the step to come is zero
+// between steps, else a step fills it first
+bool partners_clear(const ecr_run *r) {
+  return fused(r) && cell_grids(r) && r->L.ngrids == 2 && r->kp.cxreq && r->kp.n > 0;
+}
+int64_t grid_words(const ecr_run *r) { return r->ncell * (1 + r->p.n_species); }
+uint32_t *grid_of(ecr_run *r, int ahead) { return at<uint32_t>(r, r->L.chg[(r->chg_par + ahead) % r->L.ngrids]); }
+// the cell grids after k steps
+void turn_grids(ecr_run *r, int64_t k) {
+  if (cell_grids(r)) r->chg_par = (int)((r->chg_par + k) % r->L.ngrids);
+}
+// the current step's grid to the first place, as a captured period expects it
+void grids_home(ecr_run *r) {
+  if (r->chg_par == 0) return;
+  launch_grids_home(grid_of(r, 0), at<uint32_t>(r, r->L.chg[0]), at<uint32_t>(r, r->L.chg[1]), grid_words(r), r->stream);
+  r->chg_par = 0;
+}
 bool dep_pressure(const ecr_run *r) {
   return (r->p.process_mask & ECR_P_DEPOSIT) && (r->p.deposit_mask & (1u << ECR_F_ION_P));
 }
@@ -607,12 +629,13 @@ int64_t do_steps(ecr_run *r, StepArg stepw, int64_t n) {
     r->need_sort = false;
   }
   const bool grids = cell_grids(r);
-  uint32_t *chg_cur = grids ? at<uint32_t>(r, r->L.chg[r->chg_par]) : nullptr;
-  uint32_t *chg_next = grids ? at<uint32_t>(r, r->L.chg[1 - r->chg_par]) : nullptr;
-  const int64_t chg_words = r->ncell * (1 + r->p.n_species);
+  uint32_t *chg_cur = grids ? grid_of(r, 0) : nullptr;
+  uint32_t *chg_next = grids ? grid_of(r, 1) : nullptr;
+  const int64_t chg_words = grid_words(r);
   if (fused(r)) {
     const int64_t k = steps_together(r, n);
-    if (grids && !grids_clear(r)) launch_fill_u32(chg_next, 0u, chg_words, r->stream);
+    const bool clears = grids && r->L.ngrids == 3;
+    if (grids && !clears && !partners_clear(r)) launch_fill_u32(chg_next, 0u, chg_words, r->stream);
     if (r->kp.n > 0) {
       ProfScope ps(r, ECR_K_STEP);
       StepBatch<R> B{};
@@ -624,8 +647,8 @@ int64_t do_steps(ecr_run *r, StepArg stepw, int64_t n) {
       if (k > 1)
         launch_period<R>(B, (uint32_t)k, step_ext(r->kp), field_grids(r), dep_pressure(r), r->stream);
       else
-        launch_step<R>(B, (r->p.deposit_mask & 7u) == 3u, step_ext(r->kp), field_grids(r), chg_cur, chg_next,
-                       r->stream);
+        launch_step<R>(B, (r->p.deposit_mask & 7u) == 3u, step_ext(r->kp), field_grids(r),
+                       CellGrids{chg_cur, chg_next, clears ? grid_of(r, 2) : nullptr, chg_words}, r->stream);
     }
     if (k > 1) count_steps(r, k);
     else step_tail<R>(r, stepw, grids);
@@ -667,7 +690,7 @@ int64_t do_steps(ecr_run *r, StepArg stepw, int64_t n) {
 template <typename R>
 void step_tail(ecr_run *r, StepArg stepw, bool grids) {
   DevAccum *acc = at<DevAccum>(r, r->L.acc);
-  if (grids) r->chg_par = 1 - r->chg_par;
+  if (grids) turn_grids(r, 1);
   if (dep_pressure(r)) {
     ProfScope ps(r, ECR_K_DEPOSIT);
     launch_deposit_pressure<R>(r->kp, soa<R>(r, r->cur), at<double>(r, r->L.dens), r->stream);
@@ -677,8 +700,7 @@ void step_tail(ecr_run *r, StepArg stepw, bool grids) {
     // exchange partners, after the deposit; chg_par now names the grids of
     // the next step, which the partners' new charges update
     launch_cx_partner<R>(r->kp, soa<R>(r, r->cur), at<uint32_t>(r, r->L.chunks),
-                         at<uint32_t>(r, r->L.chg[r->chg_par]), at<uint32_t>(r, r->L.chg[1 - r->chg_par]),
-                         grids_clear(r) ? r->ncell * (1 + r->p.n_species) : 0,
+                         grid_of(r, 0), grid_of(r, 1), partners_clear(r) ? grid_words(r) : 0,
                          (r->p.flags & ECR_FLAG_EVENTS) ? at<uint8_t>(r, r->L.evlog) : nullptr, acc, stepw,
                          r->stream);
   }
@@ -738,7 +760,7 @@ void batch_steps(const std::vector<ecr_run *> &rs, const std::vector<StepArg> &s
       B.wg0[j + 1] = B.wg0[j] + (k > 1 ? step_wgs(r->kp.n) : step_wgs_one(r->kp.n));
     }
     if (k > 1) launch_period<R>(B, (uint32_t)k, false, false, false, st);
-    else launch_step<R>(B, true, false, false, nullptr, nullptr, st);
+    else launch_step<R>(B, true, false, false, CellGrids{}, st);
   }
   for (size_t i = 0; i < rs.size(); ++i) {
     if (k > 1) count_steps(rs[i], k);
@@ -794,7 +816,7 @@ constexpr size_t kMaxBatchSeen = 64;
 
 std::vector<uint64_t> batch_key(const std::vector<ecr_run *> &runs) {
   std::vector<uint64_t> k;
-  for (ecr_run *r : runs) k.push_back(r->uid << 2 | (uint64_t)r->cur << 1 | (uint64_t)r->chg_par);
+  for (ecr_run *r : runs) k.push_back(r->uid << 1 | (uint64_t)r->cur);
   return k;
 }
 
@@ -831,7 +853,7 @@ void forget_batch_graphs(const ecr_run *r) {
   std::lock_guard<std::mutex> lock(g_bgraph_mu);
   for (size_t i = 0; i < g_bgraphs.size();) {
     bool has = false;
-    for (uint64_t k : g_bgraphs[i].key) has |= (k >> 2) == r->uid;
+    for (uint64_t k : g_bgraphs[i].key) has |= (k >> 1) == r->uid;
     if (has) {
       (void)hipStreamSynchronize(g_bgraphs[i].stream);
       (void)hipGraphExecDestroy(g_bgraphs[i].ge);
@@ -848,8 +870,8 @@ void build_charge_grid(ecr_run *r) {
   if (!(r->p.flags & (ECR_FLAG_SELF_NE | ECR_FLAG_SELF_N0))) return;
   r->chg_par = 0;
   uint32_t *g = at<uint32_t>(r, r->L.chg[0]);
-  launch_fill_u32(g, 0u, r->ncell * (1 + r->p.n_species), r->stream);
-  launch_fill_u32(at<uint32_t>(r, r->L.chg[1]), 0u, r->ncell * (1 + r->p.n_species), r->stream);
+  launch_fill_u32(g, 0u, grid_words(r), r->stream);
+  launch_fill_u32(at<uint32_t>(r, r->L.chg[1]), 0u, grid_words(r), r->stream);
   if (r->fp32) launch_charge_grid<float>(r->kp, soa<float>(r, r->cur), g, r->stream);
   else launch_charge_grid<double>(r->kp, soa<double>(r, r->cur), g, r->stream);
 }
@@ -1063,11 +1085,10 @@ void release_run(ecr_run *r) {
   harvest(r);
   for (auto e : r->free_events) (void)hipEventDestroy(e);
   r->free_events.clear();
-  for (auto &row : r->gexec)
-    for (auto &g : row) {
-      if (g) (void)hipGraphExecDestroy(g);
-      g = nullptr;
-    }
+  for (auto &g : r->gexec) {
+    if (g) (void)hipGraphExecDestroy(g);
+    g = nullptr;
+  }
 }
 
 // bind run r (fresh) to the arena at device_arena and upload its tables;
@@ -1290,7 +1311,8 @@ ecr_status ecr_step_graph(ecr_run *r, int64_t n_steps) {
       n_steps -= k;
       continue;
     }
-    hipGraphExec_t &ge = r->gexec[r->cur][r->chg_par];
+    grids_home(r);
+    hipGraphExec_t &ge = r->gexec[r->cur];
     if (!ge) {
       const hipError_t e = capture_period(r, &ge);
       if (e != hipSuccess) {
@@ -1305,7 +1327,7 @@ ecr_status ecr_step_graph(ecr_run *r, int64_t n_steps) {
     r->steps += K;
     if (dep) r->dens_steps += K;
     r->cur = 1 - r->cur;  // the period's sort moved the state to the other buffer
-    if ((r->p.flags & (ECR_FLAG_SELF_NE | ECR_FLAG_SELF_N0)) && (K & 1)) r->chg_par = 1 - r->chg_par;
+    turn_grids(r, K);
     r->need_sort = false;
     n_steps -= K;
   }
@@ -1352,7 +1374,7 @@ ecr_status ecr_step_batch(ecr_run *const *runs, int32_t n_runs, int64_t n_steps,
       if (!ge) {
         // a set of runs is the same set whichever buffers its runs start from
         std::vector<uint64_t> ids;
-        for (uint64_t k : key) ids.push_back(k >> 2);
+        for (uint64_t k : key) ids.push_back(k >> 1);
         for (const auto &q : g_bseen) seen |= q == ids;
         if (!seen) {
           if (g_bseen.size() >= kMaxBatchSeen) g_bseen.erase(g_bseen.begin());
@@ -1370,6 +1392,7 @@ ecr_status ecr_step_batch(ecr_run *const *runs, int32_t n_runs, int64_t n_steps,
       n_steps -= K;
       continue;
     }
+    for (ecr_run *r : rs) grids_home(r);
     if (!ge) {
       const hipError_t e = capture_batch_period(rs, st, K, &ge);
       if (e != hipSuccess) return check_hip(rs[0], e, "batch graph capture");
@@ -1398,7 +1421,7 @@ ecr_status ecr_step_batch(ecr_run *const *runs, int32_t n_runs, int64_t n_steps,
       r->steps += K;
       if (r->p.process_mask & ECR_P_DEPOSIT) r->dens_steps += K;
       r->cur = 1 - r->cur;
-      if ((r->p.flags & (ECR_FLAG_SELF_NE | ECR_FLAG_SELF_N0)) && (K & 1)) r->chg_par = 1 - r->chg_par;
+      turn_grids(r, K);
       r->need_sort = false;
     }
     n_steps -= K;

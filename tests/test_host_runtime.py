@@ -1,6 +1,6 @@
 """The library's host code over a stub of the HIP runtime (no device): what
-the calls that hand results back do when their launch is refused, and what a
-run's end waits for."""
+the calls that hand results back do when their launch is refused, what a
+run's end waits for, how many launches a step takes."""
 import os
 import shutil
 import subprocess
@@ -24,7 +24,7 @@ import workloads as W
 L = ecr.lib()
 
 def create(n, **options):
-    P, keep = ecr.make_params(W.base_params(n, 8, 8, 16, **options))
+    P, keep = ecr.make_params(W.with_(W.base_params(n, 8, 8, 16), **options))
     need = C.c_size_t()
     assert L.ecr_footprint(C.byref(P), C.byref(need)) == 0
     arena = np.zeros(need.value, dtype=np.uint8)
@@ -112,4 +112,20 @@ stub.stub_refuse(0)
 assert L.ecr_read_tallies(run, C.byref(t)) == -3
 assert L.ecr_destroy(run) == 0
 assert stub.stub_host_frees() == 90 - 64 + 1 and stub.stub_host_allocs() == 90
+""")
+
+
+def test_a_step_with_cell_grids_is_one_launch(stub):
+    # and one for the exchange partners; a run of few particles on many cells
+    # has two grids only, and a launch that clears the next one
+    host(stub, """
+for options, n, want in ((dict(self_ne=True), 3000, 1), (dict(self_n0=True), 3000, 1),
+                         (dict(self_ne=True, self_n0=True, cx_partner=True), 3000, 2), (dict(self_ne=True), 100, 2),
+                         (dict(), 3000, 1)):
+    run, keep = create(n, process_mask=W.P_ALL | W.P_HEAT, **options)
+    assert L.ecr_step(run, 1) == 0
+    for _ in range(4):
+        before = stub.stub_launches()
+        assert L.ecr_step(run, 1) == 0
+        assert stub.stub_launches() - before == want, (options, n)
 """)
