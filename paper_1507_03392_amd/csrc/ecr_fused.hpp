@@ -169,6 +169,9 @@ __device__ __forceinline__ void collide_list(const JobPtr<R> job, const LdsAcc<R
   const uint16_t *list = item.pair;
   constexpr int kTri = (int)(offsetof(WorkList<M>, tri) / 2), kPairPool = (int)(offsetof(WorkList<M>, pair_pool) / 2),
                 kTriPool = (int)(offsetof(WorkList<M>, tri_pool) / 2);
+  // sixteen entries of each sum are this wavefront's own, so that what goes
+  // into an entry, and in what order, does not depend on the others' pace
+  const int own = (threadIdx.x >> 6) * 16 + (lane & 15);
   int i = first, sub = 0;
   while (count > 0) {
     // a triplet's collisions (a, b), (b, c), (c, a) are at dt/2
@@ -182,7 +185,7 @@ __device__ __forceinline__ void collide_list(const JobPtr<R> job, const LdsAcc<R
     collide_acc<R>(J.P, lnA, V, ia, ib, sid[ia], (double)m * J.P.nfac, tri ? 0.5 * J.P.dt : J.P.dt, step, cacc,
                    sub == 0, sub < 2);
 #pragma unroll
-    for (int c = 0; c < 5; ++c) atomicAdd(&cacc_sum[64 * c + lane], cacc[c]);
+    for (int c = 0; c < 5; ++c) atomicAdd(&cacc_sum[64 * c + own], cacc[c]);
     if (tri && sub < 2) {
       ++sub;
     } else {
@@ -258,61 +261,41 @@ __device__ __forceinline__ void add_moments(const double *cacc, double *__restri
   }
 }
 
-// several runs in one launch: run j owns workgroups [wg0[j], wg0[j+1]).  Its
-// chunks go to the workgroups after the first kBigWG in turn (there are
-// enough of them for one chunk each unless the cells fit the chunks badly),
-// the cells beyond a chunk to all of its workgroups in turn, the first
-// kBigWG having nothing else to do.  chunks(job, step, wg, stride, chunk
-// table, their number, moment slot): workgroup wg's chunks.  medium(job,
-// entries, moment slot, step): one step of a cell of up to 2 kPSlots slots.
-template <typename R, int FLD, bool EXT, bool PR, int LDSB, typename F, typename G>
-__device__ __forceinline__ void fused_wg(const StepBatch<R> &B, const uint32_t nsteps, const CellGrids &grids,
-                                         void *lds, F &&chunks, G &&medium) {
-  const uint32_t *__restrict__ chg_cur = grids.cur;
-  uint32_t *__restrict__ chg_next = grids.next;
-  __shared__ uint32_t red[kNW], gcount;
+// a cell [lo, end) of more than kPSlots slots, up to 2 kPSlots, as one entry
+__device__ __forceinline__ GroupEntry cell_entry(const KParams &P, uint32_t lo, uint32_t end) {
+  const uint32_t c = P.cellid[lo], r = c / (uint32_t)P.nx, lg = 31u - (uint32_t)__clz((int)(end - lo));
+  return {{lo, end, c - r * (uint32_t)P.nx, r % (uint32_t)P.ny, r / (uint32_t)P.ny, 0u, 0u, (1u << lg) | (1u << 16)},
+          {kNoPlace, kNoPlace},
+          {0u, 0u}};
+}
+// its moment slot, after the workgroups'
+template <typename R>
+__device__ __forceinline__ double *cell_moments(JobPtr<R> job, uint32_t lo) {
+  return job->moments + 5 * (int64_t)(kBigWG + job->windows * job->win_wgs + lo / (uint32_t)(kPSlots + 1));
+}
+
+// several runs in one launch: run j owns workgroups [wg0[j], wg0[j+1])
+struct RunWG {
+  int run;
+  uint32_t wg, nwg;
+};
+template <typename R>
+__device__ __forceinline__ RunWG run_of(const StepBatch<R> &B) {
   int run = 0;
   for (int t = 1; t < B.n; ++t) run = blockIdx.x >= B.wg0[t] ? t : run;
-  const JobPtr<R> job = (JobPtr<R>)B.job[run];
-  const uint32_t step0 = StepArg{B.stepw[run], B.step[run]}.get();
-  const uint32_t wg = blockIdx.x - B.wg0[run], nwg = B.wg0[run + 1] - B.wg0[run];
-  double *mslot = job->moments + 5 * (int64_t)wg;
-  const ChunkTable C = fresh<R>(job).C;
-  const uint64_t cnt = *(const __attribute__((address_space(4))) uint64_t *)C.cnt;
-  const uint32_t nchunk = (uint32_t)cnt, nbig = (uint32_t)(cnt >> 32);
-  if (wg >= (unsigned)kBigWG) chunks(job, step0, wg - kBigWG, nwg - kBigWG, C.chunk, nchunk, mslot);
-  for (uint32_t e = wg; e < nbig; e += nwg) {
-    const uint32_t lo = C.big[2 * e], end = C.big[2 * e + 1];
-    if (!PR && end - lo <= 2u * kPSlots) {
-      // as two chunks of one cell: its buckets and its number count from the
-      // first one's, which has none of its own
-      const KParams &P = fresh<R>(job).P;
-      const uint32_t c = P.cellid[lo], r = c / (uint32_t)P.nx, lg = 31u - (uint32_t)__clz((int)(end - lo));
-      const uint32_t x = c - r * (uint32_t)P.nx, y = r % (uint32_t)P.ny, z = r / (uint32_t)P.ny;
-      const ChunkEntry M[2] = {{lo, lo + kPSlots, x, y, z, 0u, 0u, 0u},
-                               {lo + kPSlots, end, x, y, z, 0u, 0u, (1u << lg) | (1u << 16)}};
-      for (uint32_t it = 0; it < nsteps; ++it) {
-        medium(job, M, mslot, step0 + it);
-        __syncthreads();
-      }
-      continue;
-    }
-    for (uint32_t it = 0; it < nsteps; ++it) {
-      const StepJob<R> &J = fresh<R>(job);
-      big_cell<R, FLD, EXT, PR, kNT, LDSB>(J.P, J.T, J.S, J.ef, lo, end, it + 1 == nsteps ? J.evlog : nullptr, J.acc,
-                                           J.dens, mslot, J.scratch64, step0 + it, chg_cur, chg_next,
-                                           (unsigned char *)lds, red, &gcount);
-    }
-  }
+  return {run, blockIdx.x - B.wg0[run], B.wg0[run + 1] - B.wg0[run]};
+}
+
+// clear the grid that the step before read
+__device__ __forceinline__ void clear_grid(const CellGrids &grids) {
   // the grid that the step before read, for the step to come to add to: a
   // fill of its own between two steps took 4-5 us of 61 at 600k ions, and
   // these stores, after everything that waits for a load, cost next to none
-  if (EXT && grids.clear) {
-    uint4 *c = reinterpret_cast<uint4 *>(grids.clear);
-    const int64_t n4 = grids.n / 4, i0 = (int64_t)blockIdx.x * kNT + threadIdx.x;
-    for (int64_t i = i0; i < n4; i += (int64_t)gridDim.x * kNT) c[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (i0 < grids.n - 4 * n4) grids.clear[4 * n4 + i0] = 0u;
-  }
+  if (!grids.clear) return;
+  uint4 *c = reinterpret_cast<uint4 *>(grids.clear);
+  const int64_t n4 = grids.n / 4, i0 = (int64_t)blockIdx.x * kNT + threadIdx.x;
+  for (int64_t i = i0; i < n4; i += (int64_t)gridDim.x * kNT) c[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (i0 < grids.n - 4 * n4) grids.clear[4 * n4 + i0] = 0u;
 }
 
 }  // namespace

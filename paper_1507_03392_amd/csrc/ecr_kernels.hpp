@@ -112,11 +112,19 @@ hipError_t launch_sum_moments(const double *moments, int64_t nslots, DevAccum *a
 // list names each job, its step and its first workgroup (run j owns
 // step_wgs(n_j) workgroups from wg0[j]).
 
-// The chunk table, rebuilt at every sort by launch_step_prep: cnt[0] chunks,
-// cnt[1] cells of more than kPSlots slots (first slot, end), and a word per
-// slot (bk_*): the buckets of its cell in the ordering (2^floor(log2 m) for a
-// cell of m slots, numbered from the chunk's first), its cell's number in the
-// chunk and whether it is the cell's first slot
+// The chunk table, rebuilt at every sort by launch_step_prep.  The slots are
+// cut into windows of kWinChunks chunks' slots; window w has its chunks at
+// chunk[w kWinList] in order of slot, where a workgroup of a fixed number
+// finds them: what a workgroup sums is the same from run to run.  win[w]: how
+// many chunks, and << 16 how many groups, at group[w kWinGroups], a single step
+// takes instead of them.  cnt[0] cells of more than kPSlots slots (first slot,
+// end; in any order), and a word per slot (bk_*): the buckets of its cell in
+// the ordering (2^floor(log2 m) for a cell of m slots, numbered from the
+// chunk's first), its cell's number in the chunk and whether it is the cell's
+// first slot.
+// launch_step_units, before the first single step after a sort, puts them in a
+// row: units, the chunks (of windows without groups) at flat and the groups at
+// gflat, in order of slot
 struct ChunkEntry {
   uint32_t lo, end;  // slots [lo, end)
   uint32_t x, y, z;  // the box of its cells: the lowest index along each axis,
@@ -125,9 +133,24 @@ struct ChunkEntry {
   __host__ __device__ uint32_t buckets() const { return nn & 0xffffu; }
   __host__ __device__ uint32_t cells() const { return nn >> 16; }
 };
+// up to three chunks in a row, at most 2 kPSlots slots: all of them as one
+// entry, and where the second and the third begin (or kNoPlace), counted from
+// the first slot, with the buckets and cells of the chunk before them
+struct GroupEntry {
+  ChunkEntry all;
+  uint32_t s[2], a[2];
+};
+constexpr uint32_t kNoPlace = 1u << 20;
+// what a single step's workgroups take: the first 2 pairs chunks two at a time
+// (the last of them may be missing), the others one at a time, the groups
+struct StepUnits {
+  uint32_t pairs, singles, groups, chunks;
+};
 struct ChunkTable {
-  uint32_t *cnt;
-  ChunkEntry *chunk;
+  uint32_t *cnt, *win;
+  ChunkEntry *chunk, *flat;
+  GroupEntry *group, *gflat;
+  StepUnits *units;
   uint32_t *big, *bkinfo;
 };
 __host__ __device__ constexpr uint32_t bk_pack(uint32_t first, uint32_t lg, uint32_t cell, bool head) {
@@ -138,11 +161,19 @@ __host__ __device__ constexpr uint32_t bk_lg(uint32_t w) { return (w >> 10) & 15
 __host__ __device__ constexpr uint32_t bk_cell(uint32_t w) { return (w >> 16) & 0x3ffu; }
 __host__ __device__ constexpr bool bk_head(uint32_t w) { return (w >> 31) != 0u; }
 constexpr int kPSlots = 512;  // most slots of a chunk
+constexpr int kWinChunks = 8;
+// most chunks of a window: a chunk ends half a chunk size or more from its
+// start, or the cell that would take it there begins the next one, so two in
+// a row hold half a chunk size
+constexpr int kWinList = 4 * kWinChunks + 2;
+constexpr int kWinGroups = kWinList / 2;  // fewer groups than pairs
+constexpr int kPlaces = 1024;  // workgroups of the step kernels that the chip holds at a time
 // workgroups at the front of a run's that take cells beyond a chunk only
 constexpr int kBigWG = 16;
 int64_t step_fill(int64_t n);  // slots a chunk is filled up to
-int64_t step_max_chunks(int64_t n);
+int64_t step_windows(int64_t n);
 int64_t step_max_big(int64_t n);
+uint32_t step_win_wgs(int64_t n);  // workgroups to a window's chunks
 uint32_t step_wgs(int64_t n);      // workgroups of launch_period
 uint32_t step_wgs_one(int64_t n);  // of launch_step, no more than those
 // From here a workgroup of a single step takes two chunks: 600k ions 47 us a
@@ -151,10 +182,13 @@ uint32_t step_wgs_one(int64_t n);  // of launch_step, no more than those
 constexpr int64_t kPairMin = 450000;
 __host__ __device__ constexpr bool step_pairs(int64_t n) { return n >= kPairMin; }
 void launch_step_prep(const KParams &P, ChunkTable C, hipStream_t st);
+void launch_step_units(int64_t n, ChunkTable C, hipStream_t st);
 
-// moments: step_wgs(n) slots of 5 doubles (momentum and energy sums of the
-// collisions); scratch64: n 64-bit words of sort space for pools beyond the
-// LDS
+// moments: slots of 5 doubles (momentum and energy sums of the collisions),
+// one for each of step_wgs(n) workgroups' chunks, then one for every kPSlots +
+// 1 slots, of the cell beyond kPSlots that starts there; scratch64: n 64-bit
+// words of sort space for pools beyond the LDS
+inline int64_t step_moment_slots(int64_t n) { return (int64_t)step_wgs(n) + step_max_big(n); }
 template <typename R>
 struct StepJob {
   KParams P;
@@ -166,6 +200,7 @@ struct StepJob {
   DevAccum *acc;
   double *dens, *moments;
   uint64_t *scratch64;
+  uint32_t windows, win_wgs;  // step_windows, step_win_wgs
 };
 constexpr int kMaxBatch = 32;
 template <typename R>

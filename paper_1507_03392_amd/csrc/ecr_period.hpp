@@ -383,20 +383,46 @@ k_period(StepBatch<R> B, uint32_t nsteps) {
   // pairs and triplets of the two work lists, and whether a pool changed
   __shared__ uint32_t tot[5 + kNW];
   static_assert(sizeof(OneShared<R>) <= sizeof(lds), "a medium cell's step fits");
-  fused_wg<R, FLD, EXT, PR, (int)sizeof(lds)>(
-      B, nsteps, CellGrids{}, &lds,
-      [&](const JobPtr<R> job, uint32_t step0, uint32_t e, uint32_t stride, const ChunkEntry *chunk, uint32_t nchunk,
-          double *mslot) __attribute__((always_inline)) {
-        const int turn = 64 * (int)(e % kNW);
-        for (; e < nchunk; e += stride) {
-          chunk_steps<R, FLD, EXT, PR>(job, chunk[e], mslot, step0, nsteps, lds, tot, turn);
-          __syncthreads();  // the next one reuses the LDS
-        }
-      },
-      [&](const JobPtr<R> job, const ChunkEntry(&M)[2], double *mslot, uint32_t step) __attribute__((always_inline)) {
-        chunk_step<R, FLD, EXT, false>(job, M, true, mslot, step, *(OneShared<R> *)&lds, tot + 5, tot, 0, nullptr,
-                                       nullptr);
-      });
+  __shared__ uint32_t red[kNW], gcount;
+  const RunWG own = run_of(B);
+  const JobPtr<R> job = (JobPtr<R>)B.job[own.run];
+  const uint32_t step0 = StepArg{B.stepw[own.run], B.step[own.run]}.get();
+  if (own.wg >= (uint32_t)kBigWG) {
+    // the windows' first chunks, then their second ones, ...: the workgroups
+    // that find none come last
+    const uint32_t e = own.wg - kBigWG, nw = job->windows, i0 = e / nw, w = e - i0 * nw;
+    const uint32_t nchunk = ((const __attribute__((address_space(4))) uint32_t *)job->C.win)[w] & 0xffffu;
+    const ChunkEntry *chunk = job->C.chunk + (size_t)w * kWinList;
+    double *mslot = job->moments + 5 * (int64_t)own.wg;
+    const int turn = 64 * (int)(e % kNW);
+    for (uint32_t i = i0; i < nchunk; i += job->win_wgs) {
+      chunk_steps<R, FLD, EXT, PR>(job, chunk[i], mslot, step0, nsteps, lds, tot, turn);
+      __syncthreads();  // the next one reuses the LDS
+    }
+  }
+  // the cells beyond a chunk, by all of the run's workgroups in turn
+  const ChunkTable C = fresh<R>(job).C;
+  const uint32_t nbig = *(const __attribute__((address_space(4))) uint32_t *)C.cnt;
+  for (uint32_t e = own.wg; e < nbig; e += own.nwg) {
+    const uint32_t lo = C.big[2 * e], end = C.big[2 * e + 1];
+    double *mslot = cell_moments<R>(job, lo);
+    const bool row = !PR && end - lo <= 2u * kPSlots;
+    const GroupEntry G = cell_entry(fresh<R>(job).P, lo, end);
+    for (uint32_t it = 0; it < nsteps; ++it) {
+      if (row) {
+        const ChunkEntry M[2] = {G.all, G.all};
+        chunk_step<R, FLD, EXT, false, true>(job, M, true, G, mslot, step0 + it, *(OneShared<R> *)&lds, tot + 5, tot, 0,
+                                             nullptr, nullptr);
+        __syncthreads();
+      } else {
+        const StepJob<R> &J = fresh<R>(job);
+        big_cell<R, FLD, EXT, PR, kNT, (int)sizeof(lds)>(J.P, J.T, J.S, J.ef, lo, end,
+                                                         it + 1 == nsteps ? J.evlog : nullptr, J.acc, J.dens, mslot,
+                                                         J.scratch64, step0 + it, nullptr, nullptr,
+                                                         (unsigned char *)&lds, red, &gcount);
+      }
+    }
+  }
 }
 
 }  // namespace

@@ -2,8 +2,9 @@
 // in one launch per step: what runs with cell grids take (they couple the
 // chunks at every step) and calls of a single step.
 //
-// A workgroup takes one chunk of whole cells, or two of them in large runs,
-// kORounds rounds of kNT slots.  The steps are those of ecr_fused.hpp, with
+// A workgroup takes one chunk of whole cells, or in large runs two of them, or
+// up to three in a row, kORounds rounds of kNT slots.  The steps are those of
+// ecr_fused.hpp, with
 // two differences: all wavefronts make the order, whose arrays lie where the
 // velocities go after it, and the deposit adds within the step, through a
 // brick over everything that the pushed chunk no longer needs.
@@ -43,19 +44,23 @@ struct OneShared {
 using EntryPtr = const __attribute__((address_space(4))) ChunkEntry *;
 __device__ __forceinline__ ChunkEntry entry(EntryPtr p, uint32_t e) { return ((const ChunkEntry *)p)[e]; }
 
-// one step of the chunks E[0] and, two of them, E[1]; the cell grids chg_cur
-// and chg_next (or null) are read and summed.  NQ: exactly the ion number and
-// charge are deposited.
-template <typename R, int FLD, bool EXT, bool NQ>
+// one step of the chunks E[0] and, two of them, E[1]; ROW: of the group (or
+// cell) E[0], its slots past kPSlots in the second half of the workgroup's
+// places, whose chunks begin at G.s; the cell grids chg_cur and chg_next (or
+// null) are read and summed.  NQ: exactly the ion number and charge are
+// deposited.
+template <typename R, int FLD, bool EXT, bool NQ, bool ROW>
 __device__ __forceinline__ void chunk_step(const JobPtr<R> job, const ChunkEntry (&E)[2], const bool two,
-                                           double *__restrict__ mslot, const uint32_t step, OneShared<R> &sh,
+                                           const GroupEntry &G, double *__restrict__ mslot, const uint32_t step, OneShared<R> &sh,
                                            uint32_t *wsum, uint32_t *tot, const int turn,
                                            const uint32_t *__restrict__ chg_cur, uint32_t *__restrict__ chg_next) {
   const int tid = threadIdx.x;
-  const int64_t lo[2] = {E[0].lo, two ? E[1].lo : 0u};
-  const int n[2] = {(int)(E[0].end - E[0].lo), two ? (int)(E[1].end - E[1].lo) : 0};
-  const int nb0 = (int)E[0].buckets(), nh0 = (int)E[0].cells();
-  const int nb = nb0 + (two ? (int)E[1].buckets() : 0), nh = nh0 + (two ? (int)E[1].cells() : 0);
+  const int64_t lo[2] = {E[0].lo, ROW ? E[0].lo + kPSlots : two ? E[1].lo : 0u};
+  const int n0 = (int)(E[0].end - E[0].lo);
+  const int n[2] = {ROW ? min(n0, kPSlots) : n0, ROW ? max(n0 - kPSlots, 0) : two ? (int)(E[1].end - E[1].lo) : 0};
+  const int nb0 = ROW ? 0 : (int)E[0].buckets(), nh0 = ROW ? 0 : (int)E[0].cells();
+  const int nb = ROW ? (int)E[0].buckets() : nb0 + (two ? (int)E[1].buckets() : 0);
+  const int nh = ROW ? (int)E[0].cells() : nh0 + (two ? (int)E[1].cells() : 0);
   const bool coul = (job->P.pmask & P_COULOMB) != 0 && n[0] + n[1] >= 2;
   const bool mcc = needs_mcc_uniform(fresh<R>(job).P);
   const uint32_t dm = job->dens ? (NQ ? 3u : job->P.dmask & 7u) : 0u;
@@ -89,6 +94,10 @@ __device__ __forceinline__ void chunk_step(const JobPtr<R> job, const ChunkEntry
       for (int k = 0; k < kCRounds; ++k) {
         qs[c * kCRounds + k] = S.qs[t[k]];
         bk[c * kCRounds + k] = bkinfo[t[k]];
+        if (ROW) {
+          const uint32_t q = (uint32_t)(tid + (c * kCRounds + k) * kNT);
+          bk[c * kCRounds + k] += (q >= G.s[0] ? G.a[0] : 0u) + (q >= G.s[1] ? G.a[1] : 0u);
+        }
       }
 #pragma unroll
       for (int k = 0; k < kCRounds; ++k) {
@@ -250,9 +259,12 @@ __device__ __forceinline__ void chunk_step(const JobPtr<R> job, const ChunkEntry
     const int cap = OneShared<R>::kBrick / nf;
     int ba[6], bb[6], u[6];
     cell_box(E[0], ba);
-    box[0] = make_box(P, ba, two ? cap / 2 : cap);
+    box[0] = make_box(P, ba, two && !ROW ? cap / 2 : cap);
     box[1] = Box{0, 0, 0, 1, 1, 0};
-    if (two) {
+    if (ROW) {
+      box[1] = box[0];
+      one_box = true;
+    } else if (two) {
       cell_box(E[1], bb);
       box[1] = make_box(P, bb, cap / 2);
 #pragma unroll
@@ -352,31 +364,65 @@ k_step(StepBatch<R> B, CellGrids grids) {
   __shared__ __align__(16) OneShared<R> sh;
   __shared__ uint32_t wsum[kNW], tot[2];
   static_assert(sizeof(sh) + 64 <= 40 * 1024, "four workgroups share a CU's 160 KB");
-  fused_wg<R, FLD, EXT, false, (int)sizeof(sh)>(
-      B, 1u, grids, &sh,
-      [&](const JobPtr<R> job, uint32_t step, uint32_t e, uint32_t stride, const ChunkEntry *table, uint32_t nchunk,
-          double *mslot) __attribute__((always_inline)) {
-        const int turn = 64 * (int)(e % kNW);
-        const uint32_t per = step_pairs(job->P.n) ? 2u : 1u;
-        const EntryPtr chunk = (EntryPtr)table;
-        e *= per;
-        // the table has room for these two whatever it holds; their loads do
-        // not wait for the number of chunks
-        ChunkEntry E[2] = {entry(chunk, e), entry(chunk, e + 1)};
-        while (e < nchunk) {
-          chunk_step<R, FLD, EXT, NQ>(job, E, per == 2u && e + 1 < nchunk, mslot, step, sh, wsum, tot, turn, grids.cur,
-                                      grids.next);
-          __syncthreads();  // the next ones reuse the LDS
-          e += per * stride;
-          if (e < nchunk) {
-            E[0] = entry(chunk, e);
-            E[1] = entry(chunk, min(e + 1, nchunk - 1));
-          }
-        }
-      },
-      [&](const JobPtr<R> job, const ChunkEntry(&M)[2], double *mslot, uint32_t step) __attribute__((always_inline)) {
-        chunk_step<R, FLD, EXT, NQ>(job, M, true, mslot, step, sh, wsum, tot, 0, grids.cur, grids.next);
-      });
+  __shared__ uint32_t red[kNW], gcount;
+  const RunWG own = run_of(B);
+  const JobPtr<R> job = (JobPtr<R>)B.job[own.run];
+  const uint32_t step = StepArg{B.stepw[own.run], B.step[own.run]}.get();
+  const ChunkTable C = fresh<R>(job).C;
+  const EntryPtr table = (EntryPtr)C.flat;
+  const uint32_t per = step_pairs(job->P.n) ? 2u : 1u;
+  uint32_t u = own.wg - kBigWG;  // (the first kBigWG: none)
+  // the table has room for these two whatever it holds; their loads do not
+  // wait for the number of chunks
+  const uint32_t at = own.wg >= (uint32_t)kBigWG ? per * u : 0u;
+  ChunkEntry E[2] = {entry(table, at), entry(table, at + 1)};
+  const StepUnits N = *(const StepUnits *)(const __attribute__((address_space(4))) StepUnits *)C.units;
+  const uint32_t nbig = *(const __attribute__((address_space(4))) uint32_t *)C.cnt;
+  const uint32_t chunked = N.pairs + N.singles, units = chunked + N.groups;
+  if (own.wg >= (uint32_t)kBigWG)
+    for (; u < chunked; u += own.nwg - kBigWG) {
+      const bool pair = u < N.pairs;
+      const uint32_t a = pair ? 2u * u : u + N.pairs, b = min(a + 1u, N.chunks - 1u);
+      if (a != at) {
+        E[0] = entry(table, a);
+        E[1] = entry(table, b);
+      }
+      chunk_step<R, FLD, EXT, NQ, false>(job, E, pair && a + 1u < N.chunks, GroupEntry{}, job->moments + 5 * (int64_t)own.wg,
+                                         step, sh, wsum, tot, 64 * (int)(own.wg % kNW), grids.cur, grids.next);
+      __syncthreads();  // the next ones reuse the LDS
+    }
+  else
+    u = units;
+  // the groups, after the chunks; the cells beyond a chunk, by all of the run's
+  // workgroups in turn
+  for (uint32_t e = own.wg; u < units || e < nbig;) {
+    GroupEntry G;
+    double *mslot;
+    bool row = true;
+    if (u < units) {
+      G = ((const GroupEntry *)(const __attribute__((address_space(4))) GroupEntry *)C.gflat)[u - chunked];
+      mslot = job->moments + 5 * (int64_t)own.wg;
+      u += own.nwg - kBigWG;
+    } else {
+      const uint32_t lo = C.big[2 * e], end = C.big[2 * e + 1];
+      row = end - lo <= 2u * kPSlots;
+      G = cell_entry(fresh<R>(job).P, lo, end);
+      mslot = cell_moments<R>(job, lo);
+      e += own.nwg;
+    }
+    if (row) {
+      const ChunkEntry M[2] = {G.all, G.all};
+      chunk_step<R, FLD, EXT, NQ, true>(job, M, G.all.end - G.all.lo > (uint32_t)kPSlots, G, mslot, step, sh, wsum, tot,
+                                        64 * (int)(own.wg % kNW), grids.cur, grids.next);
+      __syncthreads();
+    } else {
+      const StepJob<R> &J = fresh<R>(job);
+      big_cell<R, FLD, EXT, false, kNT, (int)sizeof(sh)>(J.P, J.T, J.S, J.ef, G.all.lo, G.all.end, J.evlog, J.acc, J.dens,
+                                                         mslot, J.scratch64, step, grids.cur, grids.next,
+                                                         (unsigned char *)&sh, red, &gcount);
+    }
+  }
+  if (EXT) clear_grid(grids);
 }
 
 }  // namespace

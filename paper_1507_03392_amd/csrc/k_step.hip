@@ -19,13 +19,8 @@ namespace {
 // that spans two planes is a whole plane wide, too wide for the deposit's
 // brick.
 // ---------------------------------------------------------------------------
-constexpr int kWinChunks = 8;
 constexpr int kWinMax = kWinChunks * kPSlots;  // a window's slots, its last cell's overhang left out
-constexpr int kWinWords = kWinMax / 64 + 1;    // the bit of slot kWinMax may mark the end
-// most chunks of a window: a chunk ends half a chunk size or more from its
-// start, or the cell that would take it there begins the next one, so two in
-// a row hold half a chunk size
-constexpr int kWinList = 4 * kWinChunks + 2;
+constexpr int kWinWords = kWinMax / 64;
 
 constexpr int kPrepNT = 1024;
 
@@ -37,7 +32,8 @@ __global__ void __launch_bounds__(kPrepNT) k_step_prep(KParams P, int fill, Chun
   __shared__ uint32_t wpre[kWinWords + 1], nbs[kWinMax + 1], wsum[kPrepNT / 64];
   __shared__ uint16_t cs[kWinMax + 1];
   __shared__ int8_t ck[kWinMax];  // a cell's chunk, -1 for a big cell
-  __shared__ int ncb, nbg, cbase, bbase;
+  __shared__ int ncb, nbg, bbase, ngr;
+  __shared__ uint8_t gr[kWinList + 1];  // the groups' first chunks
   __shared__ int cb[kWinList], ce[kWinList], box[kWinList][6], bc[kWinChunks + 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int64_t win = (int64_t)kWinChunks * fill;
@@ -48,12 +44,15 @@ __global__ void __launch_bounds__(kPrepNT) k_step_prep(KParams P, int fill, Chun
     return st == (uint32_t)t ? t : (int64_t)cell_off[c + 1];
   };
   const int64_t lo = first_cell(blockIdx.x * win), hi = first_cell((blockIdx.x + 1) * win);
-  if (hi <= lo) return;
+  if (hi <= lo) {
+    if (tid == 0) C.win[blockIdx.x] = 0u;
+    return;
+  }
   const int total = (int)(hi - lo);
   // heads among the window's own slots (a cell starts before the window's end)
   const int len = (int)min(hi - lo, win);
 #pragma unroll
-  for (int k = 0; k <= kWinMax / kPrepNT; ++k) {
+  for (int k = 0; k < kWinMax / kPrepNT; ++k) {
     const int i = tid + k * kPrepNT;
     uint32_t c = 0, p = 0;
     if (i < len) {
@@ -61,7 +60,7 @@ __global__ void __launch_bounds__(kPrepNT) k_step_prep(KParams P, int fill, Chun
       p = i > 0 ? cellid[lo + i - 1] : c + 1u;
     }
     const uint64_t b = __ballot(c != p), q = __ballot(c != p && i > 0 && c / plane != p / plane);
-    if (lane == 0 && (i >> 6) < kWinWords) {
+    if (lane == 0) {
       head[i >> 6] = b;
       phead[i >> 6] = q;
       wpre[i >> 6] = (uint32_t)__popcll(b);
@@ -150,8 +149,24 @@ __global__ void __launch_bounds__(kPrepNT) k_step_prep(KParams P, int fill, Chun
     if (lane == 0) {
       ncb = k;
       nbg = g;
-      cbase = (int)atomicAdd(&C.cnt[0], (uint32_t)k);
-      if (g) bbase = (int)atomicAdd(&C.cnt[1], (uint32_t)g);
+      if (g) bbase = (int)atomicAdd(&C.cnt[0], (uint32_t)g);
+      // Cells of a third of a chunk and more leave the chunks short: a
+      // workgroup of a single step then takes up to three in a row, as its room
+      // holds, instead of two (5M ions, 290 a cell: 248 us a step with pairs,
+      // 223 with groups)
+      int m = 0;
+      if (step_pairs(n)) {
+        for (int j = 0; j < k; ++m) {
+          gr[m] = (uint8_t)j;
+          const int f = j, s0 = cs[cb[j]];
+          do ++j;
+          while (j < k && j - f < 3 && cb[j] == ce[j - 1] && cell_end(ce[j] - 1) - s0 <= 2 * kPSlots);
+        }
+        gr[m] = (uint8_t)k;
+        if (m >= (k + 1) / 2) m = 0;
+      }
+      ngr = m;
+      C.win[blockIdx.x] = (uint32_t)(k | (m << 16));
     }
   }
   __syncthreads();
@@ -184,16 +199,34 @@ __global__ void __launch_bounds__(kPrepNT) k_step_prep(KParams P, int fill, Chun
     if (lane < 6) box[k][lane] = lane == 0 ? b[0] : lane == 1 ? b[1] : lane == 2 ? b[2] : lane == 3 ? b[3] : lane == 4 ? b[4] : b[5];
   }
   __syncthreads();
-  if (tid < ncb) {
-    const int *b = box[tid];
-    C.chunk[cbase + tid] = {(uint32_t)(lo + cs[cb[tid]]),
-                            (uint32_t)(lo + cell_end(ce[tid] - 1)),
-                            (uint32_t)b[0],
-                            (uint32_t)b[1],
-                            (uint32_t)b[2],
-                            (uint32_t)(min(b[3] - b[0], 0xffff) | (min(b[4] - b[1], 0xffff) << 16)),
-                            (uint32_t)min(b[5] - b[2], 0xffff),
-                            (nbs[ce[tid]] - nbs[cb[tid]]) | ((uint32_t)(ce[tid] - cb[tid]) << 16)};
+  // chunks t0 up to t1 in one entry
+  const auto entry_of = [&](int t0, int t1) -> ChunkEntry {
+    int b[6];
+    for (int d = 0; d < 6; ++d) b[d] = box[t0][d];
+    for (int t = t0 + 1; t < t1; ++t)
+      for (int d = 0; d < 3; ++d) {
+        b[d] = min(b[d], box[t][d]);
+        b[3 + d] = max(b[3 + d], box[t][3 + d]);
+      }
+    const int h0 = cb[t0], h1 = ce[t1 - 1];
+    return {(uint32_t)(lo + cs[h0]),
+            (uint32_t)(lo + cell_end(h1 - 1)),
+            (uint32_t)b[0],
+            (uint32_t)b[1],
+            (uint32_t)b[2],
+            (uint32_t)(min(b[3] - b[0], 0xffff) | (min(b[4] - b[1], 0xffff) << 16)),
+            (uint32_t)min(b[5] - b[2], 0xffff),
+            (nbs[h1] - nbs[h0]) | ((uint32_t)(h1 - h0) << 16)};
+  };
+  if (tid < ncb) C.chunk[(int64_t)blockIdx.x * kWinList + tid] = entry_of(tid, tid + 1);
+  if (tid < ngr) {
+    const int t0 = gr[tid], t1 = gr[tid + 1];
+    GroupEntry g{entry_of(t0, t1), {kNoPlace, kNoPlace}, {0u, 0u}};
+    for (int t = t0 + 1; t < t1; ++t) {
+      g.s[t - t0 - 1] = (uint32_t)((int)cs[cb[t]] - (int)cs[cb[t0]]);
+      g.a[t - t0 - 1] = (nbs[cb[t]] - nbs[cb[t - 1]]) | ((uint32_t)(cb[t] - cb[t - 1]) << 16);
+    }
+    C.group[(int64_t)blockIdx.x * kWinGroups + tid] = g;
   }
   for (int i = tid; i < total; i += kPrepNT) {
     // the slot's cell: the last head at or before it
@@ -219,22 +252,104 @@ int64_t step_fill(int64_t n) {
   return p;
 }
 
-static int64_t step_windows(int64_t n) {
+int64_t step_windows(int64_t n) {
   const int64_t w = kWinChunks * step_fill(n);
   return (n + w - 1) / w;
 }
 
-int64_t step_max_chunks(int64_t n) { return step_windows(n) * kWinList; }
 int64_t step_max_big(int64_t n) { return n / kPSlots + 1; }
 
-// a quarter more workgroups than full chunks, or than pairs of them
-uint32_t step_wgs(int64_t n) {
-  const int64_t f = step_fill(n);
-  return (uint32_t)(kBigWG + (5 * n + 4 * f - 1) / (4 * f));
+// Nine chunks to a window mostly, up to sixteen where the cells are just over
+// half a chunk.  A workgroup that finds none ends at once, so runs that leave
+// the chip's 1024 places idle take as many as they may need: two chunks in a
+// row in one workgroup cost such a launch twice the time (75k ions in cells of
+// 285, one step: 34 us with 183 workgroups for 263 chunks, 21 with enough)
+uint32_t step_win_wgs(int64_t n) {
+  const int64_t w = step_windows(n), idle = w > 0 ? (kPlaces - kBigWG) / w : 0;
+  return (uint32_t)(idle < 11 ? 11 : (idle > 2 * kWinChunks + 1 ? 2 * kWinChunks + 1 : idle));
 }
+uint32_t step_wgs(int64_t n) { return (uint32_t)(kBigWG + step_windows(n) * step_win_wgs(n)); }
 uint32_t step_wgs_one(int64_t n) {
-  const int64_t f = step_fill(n) * (step_pairs(n) ? 2 : 1);
-  return (uint32_t)(kBigWG + (5 * n + 4 * f - 1) / (4 * f));
+  return step_pairs(n) ? (uint32_t)(kBigWG + (step_windows(n) * 11 + 1) / 2) : step_wgs(n);
+}
+
+// ---------------------------------------------------------------------------
+// The single step's units.  Each workgroup adds up the counts of all windows
+// and of those before its own (489 of them at 2M ions), and moves its windows'
+// entries to their places.  Neighbours share nodes of the density, and
+// workgroups that add to the same nodes at the same time wait for each other:
+// the row is dealt out in nine turns, so that neighbours are a ninth of it
+// apart (a settled 2M run, one step: 104 us in order of slot, 98 dealt out).
+// ---------------------------------------------------------------------------
+constexpr int kUnitWins = 16;  // windows to a workgroup
+__device__ __forceinline__ uint32_t dealt(uint32_t i, uint32_t n) {
+  const uint32_t t = i % 9u;
+  return t * (n / 9u) + min(t, n % 9u) + i / 9u;
+}
+
+__global__ void __launch_bounds__(256) k_step_units(uint32_t windows, bool pairs, ChunkTable C) {
+  __shared__ uint32_t part[4][4], c0[kUnitWins + 1], g0[kUnitWins + 1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t w0 = blockIdx.x * kUnitWins;
+  const auto count = [&](uint32_t w, uint32_t &wc, uint32_t &wg) {
+    const uint32_t v = C.win[w];
+    wg = v >> 16;
+    wc = wg ? 0u : v & 0xffffu;
+  };
+  uint32_t sum[4] = {0u, 0u, 0u, 0u};  // chunks and groups before, in all
+  for (uint32_t w = tid; w < windows; w += 256) {
+    uint32_t wc, wg;
+    count(w, wc, wg);
+    sum[2] += wc;
+    sum[3] += wg;
+    if (w < w0) {
+      sum[0] += wc;
+      sum[1] += wg;
+    }
+  }
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t v = wave_incl_scan(sum[k]);
+    if (lane == 63) part[k][tid >> 6] = v;
+  }
+  __syncthreads();
+  for (int k = 0; k < 4; ++k) sum[k] = part[k][0] + part[k][1] + part[k][2] + part[k][3];
+  const uint32_t nc = sum[2], ng = sum[3];
+  if (tid == 0) {
+    for (int k = 0; k <= kUnitWins; ++k) {
+      c0[k] = sum[0];
+      g0[k] = sum[1];
+      uint32_t wc = 0, wg = 0;
+      if (w0 + k < windows) count(w0 + k, wc, wg);
+      sum[0] += wc;
+      sum[1] += wg;
+    }
+    if (blockIdx.x == 0) {
+      // pairs fill the chip's places so many times over; a small rest ends
+      // sooner in single chunks (1M ions, one step: 59 us with 76 pairs left
+      // over after one time, 54 with their chunks; 4M, 300 after four: 163
+      // and 170)
+      const uint32_t p = pairs ? (nc + 1u) / 2u : 0u, turns = (p + ng) / kPlaces, rest = (p + ng) % kPlaces;
+      const uint32_t np = turns >= 1u && turns < 8u && rest * turns * turns * turns < 480u ? p - min(p, rest) : p;
+      *C.units = {np, nc > 2u * np ? nc - 2u * np : 0u, ng, nc};
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < kUnitWins * kWinList; i += 256) {
+    const int k = i / kWinList, j = i - k * kWinList;
+    const int64_t w = w0 + k;
+    const uint32_t c = c0[k] + j, g = g0[k] + j, whole = nc / 2u;
+    if (c < c0[k + 1]) {
+      const uint32_t to = !pairs ? dealt(c, nc) : c / 2u < whole ? 2u * dealt(c / 2u, whole) + (c & 1u) : c;
+      C.flat[to] = C.chunk[w * kWinList + j];
+    }
+    if (j < kWinGroups && g < g0[k + 1]) C.gflat[dealt(g, ng)] = C.group[w * kWinGroups + j];
+  }
+}
+
+void launch_step_units(int64_t n, ChunkTable C, hipStream_t st) {
+  const uint32_t w = (uint32_t)step_windows(n);
+  if (w > 0)
+    hipLaunchKernelGGL(k_step_units, dim3((w + kUnitWins - 1) / kUnitWins), dim3(256), 0, st, w, step_pairs(n), C);
 }
 
 void launch_step_prep(const KParams &P, ChunkTable C, hipStream_t st) {

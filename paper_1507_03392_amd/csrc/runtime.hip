@@ -37,7 +37,7 @@ struct Layout {
   size_t soa[2][9];  // offsets of x y z vx vy vz qs pid birth in buffer A and B
   size_t key, rank, cellid, chunks, pairs, tris, moments, count, cell_off, bsum, dens, acc, tables, stepc, job, efield,
       bfield, evlog;
-  size_t pcnt, pchunk, pbig;  // the fused step's chunk table (its per-slot buckets reuse the sort's rank array)
+  size_t pcnt, pwin, pchunk, pgroup, punits, pflat, pgflat, pbig;  // the fused step's chunk table (its per-slot buckets reuse the sort's rank array)
   size_t scratch64;  // sort space of the pools that exceed the LDS (fused kernel)
   size_t chg[3];  // ion charge per cell, of the steps in turn (ECR_FLAG_SELF_NE)
   int ngrids;     // two or three of them
@@ -51,7 +51,7 @@ int64_t ncells(const ecr_params *p) { return (int64_t)p->nx * p->ny * p->nz; }
 // FP64 moment slots in use by a run: the Coulomb kernels' or the fused step's
 int64_t moment_slots(const ecr_params *p) {
   const int64_t m = p->n_particles > 0 ? p->n_particles : 1;
-  return p->flags & ECR_FLAG_SPLIT ? coul_moment_slots(m) : (int64_t)step_wgs(m);
+  return p->flags & ECR_FLAG_SPLIT ? coul_moment_slots(m) : step_moment_slots(m);
 }
 int64_t nnodes(const ecr_params *p) { return (int64_t)(p->nx + 1) * (p->ny + 1) * (p->nz + 1); }
 // the heating kick reads |B| hx per cell when n_e comes from the particles
@@ -88,8 +88,15 @@ Layout make_layout(const ecr_params *p) {
   o = align_up(o + 8 * N);
   // the separate kernels' work items, or the fused step's chunk table
   L.pairs = L.pcnt = o;
-  L.pchunk = align_up(L.pcnt + 8);
-  L.pbig = align_up(L.pchunk + sizeof(ChunkEntry) * (size_t)step_max_chunks((int64_t)N));
+  const size_t windows = (size_t)step_windows((int64_t)N), gwin = step_pairs((int64_t)N) ? windows : 0;
+  const size_t chunks = sizeof(ChunkEntry) * kWinList * windows, groups = sizeof(GroupEntry) * kWinGroups * gwin;
+  L.pwin = align_up(L.pcnt + 8);
+  L.pchunk = align_up(L.pwin + 4 * windows);
+  L.pgroup = align_up(L.pchunk + chunks);
+  L.punits = align_up(L.pgroup + groups);
+  L.pflat = align_up(L.punits + sizeof(StepUnits));
+  L.pgflat = align_up(L.pflat + chunks);
+  L.pbig = align_up(L.pgflat + groups);
   const size_t table_end = align_up(L.pbig + 8 * (size_t)step_max_big((int64_t)N));
   const size_t grid = 4 * (size_t)ncells(p) * (size_t)(1 + p->n_species);
   o = align_up(o + sizeof(CoulItem) * kCoulItems * (size_t)coul_nchunks((int64_t)N));
@@ -102,7 +109,7 @@ Layout make_layout(const ecr_params *p) {
   L.tris = o;  // per-chunk (pairs, triplets) counts
   o = align_up(o + 8 * (size_t)coul_nchunks((int64_t)N));
   L.moments = o;
-  o = align_up(o + 8 * 5 * (size_t)std::max(coul_moment_slots((int64_t)N), (int64_t)step_wgs((int64_t)N)));
+  o = align_up(o + 8 * 5 * (size_t)std::max(coul_moment_slots((int64_t)N), step_moment_slots((int64_t)N)));
   L.count = o;
   o = align_up(o + 4 * (size_t)(ncells(p) + 1));
   L.cell_off = o;
@@ -241,6 +248,7 @@ struct ecr_run {
   int64_t steps;
   int64_t dens_steps;
   bool need_sort;
+  bool need_units = true;  // the single step's units are not of the last sort
   bool initialized;
   bool failed;
   int cur;  // which SoA buffer is current
@@ -589,8 +597,17 @@ int64_t steps_together(const ecr_run *r, int64_t n) {
 
 // the per-slot buckets go into the sort's rank array, free until the next sort
 ChunkTable chunk_table(ecr_run *r) {
-  return {at<uint32_t>(r, r->L.pcnt), at<ChunkEntry>(r, r->L.pchunk), at<uint32_t>(r, r->L.pbig),
-          at<uint32_t>(r, r->L.rank)};
+  ChunkTable C;
+  C.cnt = at<uint32_t>(r, r->L.pcnt);
+  C.win = at<uint32_t>(r, r->L.pwin);
+  C.chunk = at<ChunkEntry>(r, r->L.pchunk);
+  C.flat = at<ChunkEntry>(r, r->L.pflat);
+  C.group = at<GroupEntry>(r, r->L.pgroup);
+  C.gflat = at<GroupEntry>(r, r->L.pgflat);
+  C.units = at<StepUnits>(r, r->L.punits);
+  C.big = at<uint32_t>(r, r->L.pbig);
+  C.bkinfo = at<uint32_t>(r, r->L.rank);
+  return C;
 }
 
 template <typename R>
@@ -606,7 +623,15 @@ void do_sort(ecr_run *r, const uint32_t *given) {
                          at<uint32_t>(r, r->L.chunks), kCoulCap, r->stream);
     if (fused(r)) launch_step_prep(r->kp, chunk_table(r), r->stream);
   }
+  r->need_units = true;
   r->cur = b;
+}
+
+// the single step's units, at its first launch after a sort
+void make_units(ecr_run *r) {
+  if (!r->need_units) return;
+  launch_step_units(r->kp.n, chunk_table(r), r->stream);
+  r->need_units = false;
 }
 
 template <typename R>
@@ -637,6 +662,7 @@ int64_t do_steps(ecr_run *r, StepArg stepw, int64_t n) {
     const bool clears = grids && r->L.ngrids == 3;
     if (grids && !clears && !partners_clear(r)) launch_fill_u32(chg_next, 0u, chg_words, r->stream);
     if (r->kp.n > 0) {
+      if (k == 1) make_units(r);
       ProfScope ps(r, ECR_K_STEP);
       StepBatch<R> B{};
       B.n = 1;
@@ -724,6 +750,8 @@ StepJob<R> make_job(ecr_run *r, int b) {
   J.dens = (r->p.process_mask & ECR_P_DEPOSIT) ? at<double>(r, r->L.dens) : nullptr;
   J.moments = at<double>(r, r->L.moments);
   J.scratch64 = at<uint64_t>(r, r->L.scratch64);
+  J.windows = (uint32_t)step_windows(r->kp.n);
+  J.win_wgs = step_win_wgs(r->kp.n);
   return J;
 }
 
@@ -748,6 +776,8 @@ void batch_steps(const std::vector<ecr_run *> &rs, const std::vector<StepArg> &s
       do_sort<R>(r, nullptr);
       r->need_sort = false;
     }
+  if (k == 1)
+    for (ecr_run *r : rs) make_units(r);
   for (size_t k0 = 0; k0 < rs.size(); k0 += kMaxBatch) {
     StepBatch<R> B{};
     B.n = (int)std::min(rs.size() - k0, (size_t)kMaxBatch);
@@ -824,10 +854,10 @@ hipError_t capture_batch_period(const std::vector<ecr_run *> &runs, hipStream_t 
   struct Saved {
     int64_t step, steps, dens;
     int cur, par;
-    bool need;
+    bool need, units;
   };
   std::vector<Saved> sv;
-  for (ecr_run *r : runs) sv.push_back({r->step, r->steps, r->dens_steps, r->cur, r->chg_par, r->need_sort});
+  for (ecr_run *r : runs) sv.push_back({r->step, r->steps, r->dens_steps, r->cur, r->chg_par, r->need_sort, r->need_units});
   hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return e;
   for (int64_t i = 0; i < K;) i += batch_steps_all(runs, st, true, (uint32_t)i, K - i);
@@ -844,6 +874,7 @@ hipError_t capture_batch_period(const std::vector<ecr_run *> &runs, hipStream_t 
     r->cur = sv[k].cur;
     r->chg_par = sv[k].par;
     r->need_sort = sv[k].need;
+    r->need_units = sv[k].units;
   }
   return e;
 }
@@ -1270,7 +1301,7 @@ hipError_t capture_period(ecr_run *r, hipGraphExec_t *out) {
   const int64_t K = r->p.sort_every;
   const int64_t step0 = r->step, steps0 = r->steps, dens0 = r->dens_steps;
   const int cur0 = r->cur, par0 = r->chg_par;
-  const bool need0 = r->need_sort;
+  const bool need0 = r->need_sort, units0 = r->need_units;
   const uint32_t *base = at<uint32_t>(r, r->L.stepc);
   hipError_t e = hipStreamBeginCapture(r->stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return e;
@@ -1289,6 +1320,7 @@ hipError_t capture_period(ecr_run *r, hipGraphExec_t *out) {
   r->cur = cur0;
   r->chg_par = par0;
   r->need_sort = need0;
+  r->need_units = units0;
   return e;
 }
 
@@ -1329,6 +1361,7 @@ ecr_status ecr_step_graph(ecr_run *r, int64_t n_steps) {
     r->cur = 1 - r->cur;  // the period's sort moved the state to the other buffer
     turn_grids(r, K);
     r->need_sort = false;
+    r->need_units = true;
     n_steps -= K;
   }
   return check_hip(r, hipGetLastError(), "graph step");
@@ -1423,6 +1456,7 @@ ecr_status ecr_step_batch(ecr_run *const *runs, int32_t n_runs, int64_t n_steps,
       r->cur = 1 - r->cur;
       turn_grids(r, K);
       r->need_sort = false;
+      r->need_units = true;
     }
     n_steps -= K;
   }
