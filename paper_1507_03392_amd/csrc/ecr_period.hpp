@@ -406,21 +406,22 @@ k_period(StepBatch<R> B, uint32_t nsteps) {
   for (uint32_t e = own.wg; e < nbig; e += own.nwg) {
     const uint32_t lo = C.big[2 * e], end = C.big[2 * e + 1];
     double *mslot = cell_moments<R>(job, lo);
-    const bool row = !PR && end - lo <= 2u * kPSlots;
-    const GroupEntry G = cell_entry(fresh<R>(job).P, lo, end);
-    for (uint32_t it = 0; it < nsteps; ++it) {
-      if (row) {
-        const ChunkEntry M[2] = {G.all, G.all};
+    if (!PR && end - lo <= 2u * kPSlots) {
+      const GroupEntry G = cell_entry(fresh<R>(job).P, lo, end);
+      const ChunkEntry M[2] = {G.all, G.all};
+      for (uint32_t it = 0; it < nsteps; ++it) {
         chunk_step<R, FLD, EXT, false, true>(job, M, true, G, mslot, step0 + it, *(OneShared<R> *)&lds, tot + 5, tot, 0,
                                              nullptr, nullptr);
         __syncthreads();
-      } else {
-        const StepJob<R> &J = fresh<R>(job);
-        big_cell<R, FLD, EXT, PR, kNT, (int)sizeof(lds)>(J.P, J.T, J.S, J.ef, lo, end,
-                                                         it + 1 == nsteps ? J.evlog : nullptr, J.acc, J.dens, mslot,
-                                                         J.scratch64, step0 + it, nullptr, nullptr,
-                                                         (unsigned char *)&lds, red, &gcount);
       }
+      continue;
+    }
+    for (uint32_t it = 0; it < nsteps; ++it) {
+      const StepJob<R> &J = fresh<R>(job);
+      big_cell<R, FLD, EXT, PR, kNT, (int)sizeof(lds)>(J.P, J.T, J.S, J.ef, lo, end,
+                                                       it + 1 == nsteps ? J.evlog : nullptr, J.acc, J.dens, mslot,
+                                                       J.scratch64, step0 + it, nullptr, nullptr, (unsigned char *)&lds,
+                                                       red, &gcount);
     }
   }
 }
