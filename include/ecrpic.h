@@ -342,7 +342,7 @@ enum {
   ECR_K_COULOMB = 1,    /* Coulomb pairing: pool order and pair lists */
   ECR_K_PUSH = 2,       /* push + wall/aperture + ionisation/charge exchange */
   ECR_K_DEPOSIT = 3,    /* deposit alone (ECR_FLAG_SPLIT) */
-  ECR_K_FUSED = 4,      /* push + wall/aperture + ionisation/charge exchange + deposit in one kernel */
+  ECR_K_FUSED = 4,      /* (push and deposit in one kernel: no longer a kernel of its own, always zero) */
   ECR_K_COUL_PAIRS = 5, /* Coulomb scattering of the listed pairs */
   ECR_K_PARTNER = 6,    /* exchange partners (ECR_FLAG_CX_PARTNER) */
   ECR_K_STEP = 7,       /* the whole step in one kernel: Coulomb pairing and collisions, push, loss, MCC, deposit */

@@ -56,8 +56,7 @@ void launch_init(const KParams &P, Soa<R> S, hipStream_t st);
 // the updated charges are summed per cell into chg_next (zeroed before)
 template <typename R>
 void launch_push(const KParams &P, const Tables *T, Soa<R> S, const double *ef, uint8_t *evlog,
-                 DevAccum *acc, double *dens, StepArg step, const uint32_t *chg_cur, uint32_t *chg_next,
-                 hipStream_t st);
+                 DevAccum *acc, StepArg step, const uint32_t *chg_cur, uint32_t *chg_next, hipStream_t st);
 
 // exchange partners (ECR_FLAG_CX_PARTNER): per Coulomb chunk, the atoms of
 // each requesting collision cell become ions in (key, id) order; chg is the

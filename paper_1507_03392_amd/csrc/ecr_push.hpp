@@ -298,25 +298,20 @@ constexpr int kStage = kPad(kTile);
 // unpadded: the push writes one slot per lane (consecutive addresses), and
 // lane l reads its kP consecutive slots back with wide loads, both free of
 // bank conflicts; 31 KB in binary64, so that five workgroups share a CU
-// TILE: slots of a staged tile (kP per lane of the workgroup)
-template <typename R, int TILE = kTile>
+template <typename R>
 struct alignas(16) DepStage {
-  R t[3][TILE];
-  uint32_t c[TILE];  // pack_cell
-  uint8_t q[TILE];  // charge, or 0xFF: nothing to deposit
+  R t[3][kTile];
+  uint32_t c[kTile];  // pack_cell
+  uint8_t q[kTile];   // charge, or 0xFF: nothing to deposit
 };
 
 // the brick reuses the staging memory: 31 bytes a slot
-template <int TILE>
-constexpr int dep_brick() {
-  return 31 * TILE / (int)sizeof(double);
-}
-constexpr int kDepBrick = dep_brick<kTile>();
+constexpr int kDepBrick = 31 * kTile / (int)sizeof(double);
 
-template <typename R, int TILE = kTile>
+template <typename R>
 union DepShared {
-  DepStage<R, TILE> st;
-  double brick[dep_brick<TILE>()];
+  DepStage<R> st;
+  double brick[kDepBrick];
 };
 
 // kP consecutive staged values of lane l (16-byte aligned: kP = 4)
@@ -409,8 +404,8 @@ __device__ __forceinline__ void run_accumulate(const DepIn<R> &D, uint32_t dm, N
 // stage the deposit input of tile slot i (lane = slot layout)
 // NQ: the deposit mask is known to hold exactly the ion number and ion
 // charge fields (the default); the atom-field paths then compile away
-template <typename R, bool NQ, int TILE = kTile>
-__device__ __forceinline__ void stage_cic(const KParams &P, DepStage<R, TILE> &st, int i, R x, R y, R z, int q, int mn[3],
+template <typename R, bool NQ>
+__device__ __forceinline__ void stage_cic(const KParams &P, DepStage<R> &st, int i, R x, R y, R z, int q, int mn[3],
                                           int mx[3]) {
   int ix, iy, iz;
   R tx, ty, tz;
@@ -470,13 +465,13 @@ __device__ __forceinline__ void box_reduce(const int *box, int out[6]) {
   for (int d = 0; d < 6; ++d) out[d] = __builtin_amdgcn_readfirstlane(out[d]);
 }
 
-// deposit a staged tile; every lane of the workgroup must call it.  G: the
-// lanes' last runs are summed within groups of G lanes (G = 64: over the
-// whole wavefront) before the run's last lane in the group flushes them
-template <typename R, bool NQ, int G = 64, int NT = kBlock>
-__device__ __forceinline__ void deposit_staged(const KParams &P, double *__restrict__ dens, DepShared<R, NT * kP> &sh,
-                                               int *box, int mn[3], int mx[3]) {
-  constexpr int kBrickCap = dep_brick<NT * kP>();
+// deposit a staged tile; every lane of the workgroup must call it.  The lanes'
+// last runs are summed over the wavefront before the run's last lane flushes
+// them
+template <typename R, bool NQ>
+__device__ __forceinline__ void deposit_staged(const KParams &P, double *__restrict__ dens, DepShared<R> &sh, int *box,
+                                               int mn[3], int mx[3]) {
+  constexpr int NT = kBlock;
   const int tid = threadIdx.x;
   const uint32_t dm = NQ ? 3u : P.dmask;
   constexpr int kFields = NQ ? 2 : 3;  // brick fields
@@ -509,50 +504,31 @@ __device__ __forceinline__ void deposit_staged(const KParams &P, double *__restr
   __syncthreads();  // staging read: the brick may now reuse it
   if (!any) return;
   const int64_t nodes = (int64_t)bx * by * bz;
-  // the lanes' last runs: summed over runs of lanes (the whole wavefront,
-  // or groups of G lanes), then the last lane of each run flushes
+  // the lanes' last runs: summed over runs of lanes, then the last lane of
+  // each run flushes
   auto flush_last = [&](DepRun &L, auto &&flush) {
     const int key = (int)L.node;
     int seg;
     bool tail;
     wave_runs(key, seg, tail);
-    if constexpr (G == 64) {
-      const SegSteps st = seg_steps(seg);
-      const bool out = tail && key >= 0;
-      for (int k = 0; k < 8; ++k) {
-        if (dm & 1u) {
-          const double v = seg_scan(st, L.a[k]);
-          if (out && v != 0.0) flush(key, 0, k, v);
-        }
-        if (dm & 2u) {
-          const double v = seg_scan(st, L.b[k]);
-          if (out && v != 0.0) flush(key, 1, k, v);
-        }
-        if (dm & 4u) {
-          const double v = seg_scan(st, L.c[k]);
-          if (out && v != 0.0) flush(key, 2, k, v);
-        }
+    const SegSteps st = seg_steps(seg);
+    const bool out = tail && key >= 0;
+    for (int k = 0; k < 8; ++k) {
+      if (dm & 1u) {
+        const double v = seg_scan(st, L.a[k]);
+        if (out && v != 0.0) flush(key, 0, k, v);
       }
-    } else {
-      const GroupSteps<G> st = group_steps<G>(seg);
-      const bool out = (tail || (threadIdx.x & (G - 1)) == G - 1) && key >= 0;
-      for (int k = 0; k < 8; ++k) {
-        if (dm & 1u) {
-          const double v = group_scan<G>(st, L.a[k]);
-          if (out && v != 0.0) flush(key, 0, k, v);
-        }
-        if (dm & 2u) {
-          const double v = group_scan<G>(st, L.b[k]);
-          if (out && v != 0.0) flush(key, 1, k, v);
-        }
-        if (dm & 4u) {
-          const double v = group_scan<G>(st, L.c[k]);
-          if (out && v != 0.0) flush(key, 2, k, v);
-        }
+      if (dm & 2u) {
+        const double v = seg_scan(st, L.b[k]);
+        if (out && v != 0.0) flush(key, 1, k, v);
+      }
+      if (dm & 4u) {
+        const double v = seg_scan(st, L.c[k]);
+        if (out && v != 0.0) flush(key, 2, k, v);
       }
     }
   };
-  if (nodes <= kBrickCap / kFields) {
+  if (nodes <= kDepBrick / kFields) {
     const int nb = (int)nodes;
     for (int i = tid; i < kFields * nb; i += NT) sh.brick[i] = 0.0;
     __syncthreads();
@@ -610,7 +586,5 @@ __device__ __forceinline__ void add_charge(uint32_t *__restrict__ chg, uint32_t 
   q = seg_scan(seg_steps(seg), q);
   if (tail && cell != 0xffffffffu && q != 0u) atomicAdd(&chg[cell], q);
 }
-
-// DEP: 0 no deposit, 1 deposit with the run's mask, 2 deposit of exactly the
 
 }  // namespace ecr

@@ -1,15 +1,12 @@
 // k_particles.hip -- per-particle kernels of the ion step (Mironov et al.,
-// Sec. II): initial ions, and the kernel that pushes each particle, applies
-// the wall / aperture loss, draws ionisation or charge exchange, and
-// deposits it on the density mesh.
+// Sec. II): initial ions, the step's push and deposit as kernels of their own
+// (ECR_FLAG_SPLIT), the pressure field of a single step, the cell grids.
 //
 // Layout: structure of arrays in HBM, one lane per slot, so every load and
 // store of a wavefront is 64 consecutive elements.  A workgroup covers a tile
 // of kP x 256 slots.  Slots are in cell order (sorted every sort_every steps),
 // which the deposit exploits (see deposit_staged): it takes the deposit from
 // 16 contended global atomics per particle to a few per workgroup.
-#include <type_traits>
-
 #include "ecr_kernels.hpp"
 #include "ecr_push.hpp"
 
@@ -63,27 +60,21 @@ __global__ void __launch_bounds__(256) k_init(KParams P, Soa<R> S) {
 }
 
 // ---------------------------------------------------------------------------
-// Push + wall/aperture + MCC (+ deposit): slot j = tile + tid + 256 p.
+// Push + wall/aperture + MCC: slot j = tile + tid + 256 p.
 // ---------------------------------------------------------------------------
-// ion number and charge fields
-template <typename R, int FLD, int DEP, bool EXT>
-__device__ __forceinline__ void push_tile(const KParams &P, const Tables *__restrict__ T, Soa<R> S,
-                                          const double *__restrict__ ef, uint8_t *__restrict__ evlog,
-                                          DevAccum *__restrict__ acc, double *__restrict__ dens, StepArg sa,
-                                          const uint32_t *__restrict__ chg_cur, uint32_t *__restrict__ chg_next) {
-  __shared__ DepShared<R> sh;
+template <typename R, int FLD, bool EXT>
+__global__ void __launch_bounds__(kBlock) k_push(KParams P, const Tables *__restrict__ T, Soa<R> S,
+                                                 const double *__restrict__ ef, uint8_t *__restrict__ evlog,
+                                                 DevAccum *__restrict__ acc, StepArg sa,
+                                                 const uint32_t *__restrict__ chg_cur,
+                                                 uint32_t *__restrict__ chg_next) {
   const uint32_t step = sa.get();
-  __shared__ int box[6 * (kBlock / 64)];
-  int mn[3] = {0x7fffffff, 0x7fffffff, 0x7fffffff}, mx[3] = {-1, -1, -1};
   const int64_t base = (int64_t)blockIdx.x * kTile;
 #pragma unroll
   for (int p = 0; p < kP; ++p) {
-    const int i = threadIdx.x + p * kBlock;
-    const int64_t j = base + i;
+    const int64_t j = base + threadIdx.x + p * kBlock;
     uint32_t ccell = 0xffffffffu, cq = 0u;  // this lane's contribution to the next charge grid
-    if (j >= P.n) {
-      if (DEP) sh.st.q[i] = 0xFF;
-    } else {
+    if (j < P.n) {
       R x = S.x[j], y = S.y[j], z = S.z[j];
       R vx = S.vx[j], vy = S.vy[j], vz = S.vz[j];
       const uint8_t qs0 = S.qs[j];
@@ -108,34 +99,12 @@ __device__ __forceinline__ void push_tile(const KParams &P, const Tables *__rest
         ccell = Q >= 1 ? c : (uint32_t)(1 + s) * P.ncell + c;
         cq = Q >= 1 ? (uint32_t)Q : 1u;
       }
-      if (DEP) stage_cic<R, DEP == 2>(P, sh.st, i, x, y, z, Q, mn, mx);
     }
     if (EXT && chg_next) add_charge(chg_next, ccell, cq);  // all lanes together: run sums use shuffles
   }
-  if (DEP) deposit_staged<R, DEP == 2>(P, dens, sh, box, mn, mx);
 }
 
-template <typename R, int FLD, int DEP, bool EXT>
-__global__ void __launch_bounds__(kBlock) k_push(KParams P, const Tables *__restrict__ T, Soa<R> S,
-                                                 const double *__restrict__ ef, uint8_t *__restrict__ evlog,
-                                                 DevAccum *__restrict__ acc, double *__restrict__ dens,
-                                                 StepArg sa, const uint32_t *__restrict__ chg_cur,
-                                                 uint32_t *__restrict__ chg_next) {
-  push_tile<R, FLD, DEP, EXT>(P, T, S, ef, evlog, acc, dens, sa, chg_cur, chg_next);
-}
-
-// the default binary64 step (no E field, ion number and charge deposit, no
-// optional physics) held at five waves per SIMD: its 31 KB of LDS lets five
-// workgroups share a CU, and the registers fit with a few spills on cold paths
-// (measured 68 -> 65 us per launch at 2M ions)
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5)))
-k_push_lean(KParams P, const Tables *__restrict__ T, Soa<double> S, const double *__restrict__ ef,
-            uint8_t *__restrict__ evlog, DevAccum *__restrict__ acc, double *__restrict__ dens, StepArg sa,
-            const uint32_t *__restrict__ chg_cur, uint32_t *__restrict__ chg_next) {
-  push_tile<double, 0, 2, false>(P, T, S, ef, evlog, acc, dens, sa, chg_cur, chg_next);
-}
-
-// standalone deposit (same tile code), for per-kernel timing
+// the deposit by itself, for per-kernel timing
 template <typename R, bool NQ>
 __global__ void __launch_bounds__(kBlock) k_deposit(KParams P, Soa<R> S, double *__restrict__ dens) {
   __shared__ DepShared<R> sh;
@@ -294,47 +263,27 @@ void launch_init(const KParams &P, Soa<R> S, hipStream_t st) {
   hipLaunchKernelGGL(k_init<R>, dim3(grid_for(P.n, 256)), dim3(256), 0, st, P, S);
 }
 
-template <typename R, int FLD, bool EXT>
-static void launch_push_e(const KParams &P, const Tables *T, Soa<R> S, const double *ef, uint8_t *evlog,
-                          DevAccum *acc, double *dens, StepArg step, const uint32_t *chg_cur, uint32_t *chg_next,
-                          hipStream_t st) {
-  const dim3 g(grid_for(P.n, kTile)), b(kBlock);
-  if (!dens)
-    hipLaunchKernelGGL((k_push<R, FLD, 0, EXT>), g, b, 0, st, P, T, S, ef, evlog, acc, dens, step, chg_cur,
-                       chg_next);
-  else if ((P.dmask & 7u) == 3u) {
-    if constexpr (std::is_same<R, double>::value && FLD == 0 && !EXT)
-      hipLaunchKernelGGL(k_push_lean, g, b, 0, st, P, T, S, ef, evlog, acc, dens, step, chg_cur, chg_next);
-    else
-      hipLaunchKernelGGL((k_push<R, FLD, 2, EXT>), g, b, 0, st, P, T, S, ef, evlog, acc, dens, step, chg_cur,
-                         chg_next);
-  } else {
-    hipLaunchKernelGGL((k_push<R, FLD, 1, EXT>), g, b, 0, st, P, T, S, ef, evlog, acc, dens, step, chg_cur,
-                       chg_next);
-  }
-}
-
 template <typename R, bool EXT>
 static void launch_push_v(const KParams &P, const Tables *T, Soa<R> S, const double *ef, uint8_t *evlog,
-                          DevAccum *acc, double *dens, StepArg step, const uint32_t *chg_cur, uint32_t *chg_next,
-                          hipStream_t st) {
+                          DevAccum *acc, StepArg step, const uint32_t *chg_cur, uint32_t *chg_next, hipStream_t st) {
+  const dim3 g(grid_for(P.n, kTile)), b(kBlock);
   switch ((ef ? 1 : 0) | (P.bmap ? 2 : 0)) {
-    case 0: launch_push_e<R, 0, EXT>(P, T, S, ef, evlog, acc, dens, step, chg_cur, chg_next, st); break;
-    case 1: launch_push_e<R, 1, EXT>(P, T, S, ef, evlog, acc, dens, step, chg_cur, chg_next, st); break;
-    case 2: launch_push_e<R, 2, EXT>(P, T, S, ef, evlog, acc, dens, step, chg_cur, chg_next, st); break;
-    default: launch_push_e<R, 3, EXT>(P, T, S, ef, evlog, acc, dens, step, chg_cur, chg_next, st); break;
+    case 0: hipLaunchKernelGGL((k_push<R, 0, EXT>), g, b, 0, st, P, T, S, ef, evlog, acc, step, chg_cur, chg_next); break;
+    case 1: hipLaunchKernelGGL((k_push<R, 1, EXT>), g, b, 0, st, P, T, S, ef, evlog, acc, step, chg_cur, chg_next); break;
+    case 2: hipLaunchKernelGGL((k_push<R, 2, EXT>), g, b, 0, st, P, T, S, ef, evlog, acc, step, chg_cur, chg_next); break;
+    default: hipLaunchKernelGGL((k_push<R, 3, EXT>), g, b, 0, st, P, T, S, ef, evlog, acc, step, chg_cur, chg_next); break;
   }
 }
 
 template <typename R>
 void launch_push(const KParams &P, const Tables *T, Soa<R> S, const double *ef, uint8_t *evlog, DevAccum *acc,
-                 double *dens, StepArg step, const uint32_t *chg_cur, uint32_t *chg_next, hipStream_t st) {
+                 StepArg step, const uint32_t *chg_cur, uint32_t *chg_next, hipStream_t st) {
   if (P.n <= 0) return;
   const bool ext = chg_cur || chg_next || (P.pmask & (P_HEAT | P_ELASTIC)) || P.nion > 1;
   if (ext)
-    launch_push_v<R, true>(P, T, S, ef, evlog, acc, dens, step, chg_cur, chg_next, st);
+    launch_push_v<R, true>(P, T, S, ef, evlog, acc, step, chg_cur, chg_next, st);
   else
-    launch_push_v<R, false>(P, T, S, ef, evlog, acc, dens, step, chg_cur, chg_next, st);
+    launch_push_v<R, false>(P, T, S, ef, evlog, acc, step, chg_cur, chg_next, st);
 }
 
 // ion charge and atoms per cell of the current state (the first step after init or set_state)
@@ -409,9 +358,9 @@ template void launch_deposit_pressure<float>(const KParams &, Soa<float>, double
 template void launch_init<double>(const KParams &, Soa<double>, hipStream_t);
 template void launch_init<float>(const KParams &, Soa<float>, hipStream_t);
 template void launch_push<double>(const KParams &, const Tables *, Soa<double>, const double *, uint8_t *, DevAccum *,
-                                  double *, StepArg, const uint32_t *, uint32_t *, hipStream_t);
+                                  StepArg, const uint32_t *, uint32_t *, hipStream_t);
 template void launch_push<float>(const KParams &, const Tables *, Soa<float>, const double *, uint8_t *, DevAccum *,
-                                 double *, StepArg, const uint32_t *, uint32_t *, hipStream_t);
+                                 StepArg, const uint32_t *, uint32_t *, hipStream_t);
 template void launch_deposit<double>(const KParams &, Soa<double>, double *, hipStream_t);
 template void launch_deposit<float>(const KParams &, Soa<float>, double *, hipStream_t);
 

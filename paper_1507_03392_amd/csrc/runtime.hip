@@ -696,15 +696,14 @@ int64_t do_steps(ecr_run *r, StepArg stepw, int64_t n) {
                          at<uint2>(r, r->L.tris), at<double>(r, r->L.moments), stepw, r->stream);
   }
   const bool dep = (pm & ECR_P_DEPOSIT) != 0;
-  const bool split = (r->p.flags & ECR_FLAG_SPLIT) != 0;
   if (grids && !fold) launch_fill_u32(chg_next, 0u, chg_words, r->stream);
   {
-    ProfScope ps(r, (dep && !split) ? ECR_K_FUSED : ECR_K_PUSH);
+    ProfScope ps(r, ECR_K_PUSH);
     launch_push<R>(r->kp, T, soa<R>(r, r->cur), r->p.efield_nodes ? at<double>(r, r->L.efield) : nullptr,
-                   (r->p.flags & ECR_FLAG_EVENTS) ? at<uint8_t>(r, r->L.evlog) : nullptr, acc,
-                   (dep && !split) ? at<double>(r, r->L.dens) : nullptr, stepw, chg_cur, chg_next, r->stream);
+                   (r->p.flags & ECR_FLAG_EVENTS) ? at<uint8_t>(r, r->L.evlog) : nullptr, acc, stepw, chg_cur, chg_next,
+                   r->stream);
   }
-  if (dep && split) {
+  if (dep) {
     ProfScope ps(r, ECR_K_DEPOSIT);
     launch_deposit<R>(r->kp, soa<R>(r, r->cur), at<double>(r, r->L.dens), r->stream);
   }
