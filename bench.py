@@ -18,9 +18,9 @@ dominant kernel (algorithmic bytes per launch / its mean launch time, timed
 with HIP events on the run's stream around one in `stride` of its launches
 over the same number of steps right after the timed window, at least ten of
 them: an event-timed launch is one step, the window's launches are several)
-and of the whole step (the fused step's algorithmic bytes plus the sort's
-share, over the mean step time of the window),
-the HBM traffic the committed rocprofv3 counters give for that kernel, and
+and of the window itself (the state's bytes once per launch of the window
+plus the sort's share, over the mean step time of the window),
+the HBM traffic the committed rocprofv3 counters give for those kernels, and
 the CPU oracle timed on a bounded sample of the same workload, alone on one
 core and as one copy per usable core at once.
 """
@@ -40,6 +40,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+PERIOD_STEPS = 64  # most steps of one launch of the library
 METRIC = "ion particle-steps/s (push+MCC+deposit) at 2M ions; p50/p99 scan latency"
 
 
@@ -122,6 +123,21 @@ def measured_traffic(workload, kernel):
     if kv.get("source_sha256") != kernel_sources_sha256() or "traffic_bytes_per_launch" not in kv:
         return None
     return float(kv["traffic_bytes_per_launch"])
+
+
+def launches_per_period(params, split):
+    """Launches of a whole sort period's steps: the steps up to the next sort go
+    out together, unless grids couple the cells at every step."""
+    period = params["sort_every"]
+    if split or params.get("self_ne") or params.get("self_n0"):
+        return period
+    return -(-period // PERIOD_STEPS)
+
+
+def window_bytes(table, params, split):
+    """Algorithmic bytes per particle and step of the timed window: the state
+    once per launch, and the sort's share."""
+    return (table["step"] * launches_per_period(params, split) + table["sort"]) / params["sort_every"]
 
 
 def log(msg):
@@ -412,15 +428,16 @@ def main():
     alg = table[dom] * n
     avg_s = ms * 1e-3 / max(1, launches)
     achieved = alg / avg_s / 1e9
-    # the whole step against the roofline: the fused step's bytes plus the
-    # sort's amortised over its period
-    step_bytes = (table["step"] + table["sort"] / period) * n
+    # the window against the roofline
+    launches_of_period = launches_per_period(params, args.split)
+    step_bytes = window_bytes(table, params, args.split) * n
     step_frac = step_bytes / (elapsed / steps) / 1e9 / HBM_PEAK_GBS
     # the counters were taken on the default step (fixed electron background,
     # no optional physics, fused deposit): another configuration runs other code
     default_step = not (args.self_ne or args.heat or args.split or args.self_n0 or args.cx_partner or args.pressure
                         or args.process_mask is not None)
     traffic = measured_traffic(args.workload, dom) if default_step else None
+    period_traffic = measured_traffic(args.workload, "period") if default_step else None
 
     drift = None
     if fp32 and not args.no_drift:
@@ -474,7 +491,10 @@ def main():
         "roofline": {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "alg_bytes_per_launch": alg, "avg_launch_us": avg_s * 1e6, "timed_launches": launches,
-                     "event_stride": stride, "step_alg_bytes": step_bytes, "step_frac": step_frac},
+                     "event_stride": stride, "timed": "launches of one step, after the window",
+                     "window": {"launch_steps": period / launches_of_period, "alg_bytes_per_launch": table["step"] * n,
+                                "traffic_per_launch": period_traffic},
+                     "step_alg_bytes": step_bytes, "step_frac": step_frac},
         "kernels": kernels,
         "tallies": {"ionized": int(tal["ionized"].sum()), "wall": int(tal["wall"].sum()),
                     "extracted": int(tal["extracted"].sum()), "cx": int(tal["cx"].sum()),

@@ -4,6 +4,7 @@
   anything touches a device.
 * The HBM traffic of the dominant kernel is taken from a committed counter
   summary only while the kernel sources hash to the value stored in it.
+* The window's bytes hold the state once per launch, not once per step.
 """
 import os
 import subprocess
@@ -48,3 +49,11 @@ def test_committed_summary_names_a_hash_of_the_right_form(name):
                 kv[k.strip()] = v.strip()
     assert len(kv["source_sha256"]) == 64 and int(kv["source_sha256"], 16) >= 0
     assert float(kv["traffic_bytes_per_launch"]) > 0
+
+
+@pytest.mark.parametrize("period,more,split,launches", [
+    (50, {}, False, 1), (64, {}, False, 1), (65, {}, False, 2), (200, {}, False, 4),
+    (50, {}, True, 50), (50, {"self_ne": True}, False, 50), (50, {"self_n0": True}, False, 50)])
+def test_window_bytes_hold_the_state_once_per_launch(period, more, split, launches):
+    params = {"sort_every": period, **more}
+    assert bench.window_bytes({"step": 106, "sort": 158}, params, split) == (106 * launches + 158) / period
