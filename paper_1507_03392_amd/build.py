@@ -34,8 +34,9 @@ CFLAGS = [
 # doubling the pair kernel's register count and halving its occupancy.
 EXTRA_FLAGS = {
     "k_coulomb.hip": ["-mllvm", "-disable-machine-licm"],
-    # the fused step kernel holds the same collision loop (with LICM: 346
-    # spilled VGPRs at four waves per SIMD; without: 15)
+    # the fused step kernels hold the same collision loop.  Spilled VGPRs at
+    # four waves per SIMD, with LICM and without: 788 and 26 in k_period, 895
+    # and 12 in k_step; in binary32-mixed 286 and 3, 290 and 2
     "k_step.hip": ["-mllvm", "-disable-machine-licm"],
     "k_step_f32.hip": ["-mllvm", "-disable-machine-licm"],
 }

@@ -109,7 +109,8 @@ hipError_t launch_sum_moments(const double *moments, int64_t nslots, DevAccum *a
 // for one or several runs in a launch.  A run's arguments sit in its job in
 // device memory (written by launch_set_job, passed by value); the launch's
 // list names each job, its step and its first workgroup (run j owns
-// step_wgs(n_j) workgroups from wg0[j]).
+// step_wgs(n_j) workgroups from wg0[j] in launch_period, step_wgs_one(n_j) in
+// launch_step).
 
 // The chunk table, rebuilt at every sort by launch_step_prep.  The slots are
 // cut into windows of kWinChunks chunks' slots; window w has its chunks at
@@ -122,8 +123,8 @@ hipError_t launch_sum_moments(const double *moments, int64_t nslots, DevAccum *a
 // chunk's first), its cell's number in the chunk and whether it is the cell's
 // first slot.
 // launch_step_units, before the first single step after a sort, puts them in a
-// row: units, the chunks (of windows without groups) at flat and the groups at
-// gflat, in order of slot
+// row without gaps: units, the chunks (of windows without groups) at flat and
+// the groups at gflat, dealt out so that neighbours in space are apart
 struct ChunkEntry {
   uint32_t lo, end;  // slots [lo, end)
   uint32_t x, y, z;  // the box of its cells: the lowest index along each axis,
@@ -175,9 +176,10 @@ int64_t step_max_big(int64_t n);
 uint32_t step_win_wgs(int64_t n);  // workgroups to a window's chunks
 uint32_t step_wgs(int64_t n);      // workgroups of launch_period
 uint32_t step_wgs_one(int64_t n);  // of launch_step, no more than those
-// From here a workgroup of a single step takes two chunks: 600k ions 47 us a
-// step with one, 38 with two, 2M 112 and 88; below, half the workgroups no
-// longer fill the chip (300k: 27 us with one).
+// From here a workgroup of a single step takes two chunks: 600k ions 46 us a
+// step with one, 39 with two, 1M 64 and 54, 2M 112 and 89; below, half the
+// workgroups no longer fill the chip (300k 28 us with one, 33 with two; 450k
+// 32 and 34).
 constexpr int64_t kPairMin = 450000;
 __host__ __device__ constexpr bool step_pairs(int64_t n) { return n >= kPairMin; }
 void launch_step_prep(const KParams &P, ChunkTable C, hipStream_t st);

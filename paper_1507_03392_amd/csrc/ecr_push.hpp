@@ -1,5 +1,5 @@
 // ecr_push.hpp -- per-particle device code of the ion step (Mironov et al.,
-// Sec. II), shared by the push kernels and the fused step kernel: the
+// Sec. II), shared by the push kernel and the fused step kernels: the
 // electron-ion heating kick, the advance of one particle (push, wall and
 // aperture loss, ionisation / charge exchange / elastic scattering), and the
 // cloud-in-cell deposit of a staged tile through an LDS brick.
@@ -13,7 +13,7 @@ namespace ecr {
 constexpr int kP = 4;                // consecutive slots per lane
 constexpr int kBlock = 256;          // lanes per workgroup
 constexpr int kTile = kBlock * kP;   // slots per workgroup
-constexpr int kBrickNodes = 1536;    // LDS brick capacity in nodes (x 3 fields)
+constexpr int kBrickNodes = 1536;    // a third of the pressure deposit's LDS brick, in nodes
 
 // ---------------------------------------------------------------------------
 // Electron-ion heating and diffusion (Sec. II): dV = D (R + delta) |R| /

@@ -3,11 +3,11 @@
 // chunks at every step) and calls of a single step.
 //
 // A workgroup takes one chunk of whole cells, or in large runs two of them, or
-// up to three in a row, kORounds rounds of kNT slots.  The steps are those of
-// ecr_fused.hpp, with
-// two differences: all wavefronts make the order, whose arrays lie where the
-// velocities go after it, and the deposit adds within the step, through a
-// brick over everything that the pushed chunk no longer needs.
+// up to three in a row, kORounds rounds of kNT slots.  The parts of a step are
+// those of ecr_fused.hpp, with two differences from ecr_period.hpp: all
+// wavefronts make the order, whose arrays lie where the velocities go after
+// it, and the deposit adds within the step, through a brick over everything
+// that the pushed chunk no longer needs.
 #pragma once
 
 #include "ecr_fused.hpp"

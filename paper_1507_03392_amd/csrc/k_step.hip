@@ -1,7 +1,7 @@
 // k_step.hip -- the binary64 instances of the fused step kernels
-// (ecr_period.hpp, ecr_single.hpp), and what both precisions share: the chunk table made at
-// every sort, the size of a launch, and the small kernels that write a run's
-// job and its step word.
+// (ecr_period.hpp, ecr_single.hpp), and what both precisions share: the chunk
+// table made at every sort, the units of a single step, the size of a launch,
+// and the small kernels that write a run's job and its step word.
 #include "ecr_period.hpp"
 
 namespace ecr {
@@ -11,10 +11,11 @@ namespace {
 // ---------------------------------------------------------------------------
 // The chunk table, once per sort.  A workgroup takes a window of kWinChunks
 // chunks' slots (the cells whose first slot lies in it), marks the cells'
-// first slots in LDS, and one lane fills chunks of whole cells up to the
-// chunk size; a cell beyond it is a chunk of its own, beyond kPSlots a big
-// cell.  Filling them cell by cell leaves half a cell of a chunk empty on
-// average, where chunks of fixed first slots need a whole large cell's room.
+// first slots in LDS, and one wavefront spreads the cells over as few chunks
+// of at most the chunk size as hold them, evenly; a cell beyond that size is a
+// chunk of its own, beyond kPSlots a big cell.  Filling them cell by cell
+// leaves half a cell of a chunk empty on average, where chunks of fixed first
+// slots need a whole large cell's room.
 // A chunk at least half full ends with its plane of cells: the box of one
 // that spans two planes is a whole plane wide, too wide for the deposit's
 // brick.
@@ -245,7 +246,8 @@ __global__ void __launch_bounds__(kPrepNT) k_step_prep(KParams P, int fill, Chun
 
 // Runs from 128 full chunks up fill their chunks; a smaller run gets about
 // 128 chunks of a power-of-two size (at least 64 slots), so that it still
-// spreads over the CUs.
+// spreads over the CUs.  The line is that of a kernel of one step; other sizes
+// have not been timed with k_period.
 int64_t step_fill(int64_t n) {
   int64_t p = 64;
   while (2 * p <= n / 128 && 2 * p <= kPSlots) p *= 2;
