@@ -286,6 +286,19 @@ __device__ __forceinline__ RunWG run_of(const StepBatch<R> &B) {
   return {run, blockIdx.x - B.wg0[run], B.wg0[run + 1] - B.wg0[run]};
 }
 
+// The cell grids among the kernel's own arguments, which follow its StepBatch:
+// read again where the step clears, not kept in scalar registers (as lanes of
+// a vector register, mostly) from the kernel's start to its end.  A settled
+// run of 2M with a self-consistent n_e 110.0 -> 109.2 us a step, with the
+// heating kick 146.1 -> 144.4.
+template <typename R>
+__device__ __forceinline__ CellGrids grids_arg() {
+  static_assert(sizeof(StepBatch<R>) % alignof(CellGrids) == 0, "the second argument follows the first");
+  auto p = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(StepBatch<R>);
+  asm volatile("" : "+s"(p));
+  return *(const CellGrids *)p;
+}
+
 // clear the grid that the step before read
 __device__ __forceinline__ void clear_grid(const CellGrids &grids) {
   // the grid that the step before read, for the step to come to add to: a

@@ -422,7 +422,7 @@ k_step(StepBatch<R> B, CellGrids grids) {
                                                          (unsigned char *)&sh, red, &gcount);
     }
   }
-  if (EXT) clear_grid(grids);
+  if (EXT) clear_grid(grids_arg<R>());
 }
 
 }  // namespace
